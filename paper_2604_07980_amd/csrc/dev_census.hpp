@@ -453,7 +453,7 @@ __device__ __forceinline__ void compact_frame_tiles(const FrameDev& fr, int f, c
   int cnt = 0;
   for (int k = 0; k < wpt; ++k)
     if (w0 + k < n_words) cnt += __popc(word(w0 + k));
-  const int incl = wave_incl_scan(cnt, lane);
+  const int incl = wave_incl_scan(cnt);
   if (lane == 63) sc[wave] = incl;
   __syncthreads();
   int r = incl - cnt;

@@ -6,7 +6,12 @@
 namespace ocsr {
 namespace dev {
 
-__device__ __forceinline__ int cdiv_nonneg(int a, int s) { return (a + s - 1) / s; }
+// ceil(a / s); s is the same for the whole wave and mostly 1 or 2
+__device__ __forceinline__ int cdiv_nonneg(int a, int s) {
+  if (s == 1) return a;
+  if (s == 2) return (a + 1) >> 1;
+  return (a + s - 1) / s;
+}
 
 // A value the whole wave holds, moved to scalar registers (the compiler cannot always
 // tell that a value read through a uniformly computed index is uniform).
@@ -22,12 +27,15 @@ __device__ __forceinline__ T* uniform(T* p) {
   return (T*)(GlobalT*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(v, d, 64);
-    if (lane >= d) v += t;
-  }
+// Inclusive prefix sum over the wave: DPP shifts within rows of 16 lanes, then the last
+// lane of row 0 (2) into row 1 (3) and lane 31 into rows 2 and 3.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
   return v;
 }
 

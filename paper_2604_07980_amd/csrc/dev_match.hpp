@@ -22,18 +22,12 @@ constexpr int kAggMax = 4096;
 // ---------------------------------------------------------------------------------
 // plan: one wave walks the frame's boxes 64 at a time
 // ---------------------------------------------------------------------------------
-// With items == false the item records are left to write_frame_items. With lplan and a
-// frame of at most lcap boxes, the plans also go to lplan[i] and the running item ends of
-// the two levels to lend[i] (far) and lend[n + i] (close), and the two item counts to
-// lend[2 n] (far) and lend[2 n + 1] (close), in LDS, for write_frame_items.
 __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameDev& fr, int f,
                                            int n_total, const ocsr_box* __restrict__ boxes,
-                                           const MatchWs& ws, int lane, bool items = true,
-                                           BoxPlan* lplan = nullptr, int32_t* lend = nullptr,
-                                           int lcap = 0) {
+                                           const MatchWs& ws, int lane) {
   const int n = fr.n_boxes;
   const int W = fr.W, H = fr.H;
-  int carry = 0, carry0 = 0, carry1 = 0, matched_end = 0;
+  int carry = 0, carry0 = 0, carry1 = 0;
   // the next 64 boxes are loaded while the current ones are planned
   ocsr_box next = {};
   if (lane < n) next = boxes[fr.box_off + lane];
@@ -93,7 +87,7 @@ __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameD
       }
     }
     // block numbers: prefix over the boxes; a range passing the capacity is dropped
-    const int incl = wave_incl_scan(count, lane);
+    const int incl = wave_incl_scan(count);
     const int off = carry + incl - count;
     int nblk = 0;
     if (pl.status == -1 && i < n) {
@@ -105,8 +99,8 @@ __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameD
     const int nitem = (nblk + ib - 1) / ib;
     const int c0 = (pl.status == -1 && pl.level == 0) ? nitem : 0;
     const int c1 = (pl.status == -1 && pl.level == 1) ? nitem : 0;
-    const int incl0 = wave_incl_scan(c0, lane);
-    const int incl1 = wave_incl_scan(c1, lane);
+    const int incl0 = wave_incl_scan(c0);
+    const int incl1 = wave_incl_scan(c1);
     if (i < n) {
       const int g = fr.box_off + i;
       pl.off = off;
@@ -117,119 +111,58 @@ __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameD
       ws.clip[g] = cl;
       ws.litem_end[g] = carry0 + incl0;
       ws.litem_end[n_total + g] = carry1 + incl1;
-      if (lplan && n <= lcap) {
-        lplan[i] = pl;
-        lend[i] = carry0 + incl0;
-        lend[n + i] = carry1 + incl1;
-      }
     }
-    matched_end = max(matched_end, wave_max(nblk > 0 ? off + nblk : 0));
-    carry += __shfl(incl, 63, 64);
-    carry0 += __shfl(incl0, 63, 64);
-    carry1 += __shfl(incl1, 63, 64);
+    carry += __builtin_amdgcn_readlane(incl, 63);
+    carry0 += __builtin_amdgcn_readlane(incl0, 63);
+    carry1 += __builtin_amdgcn_readlane(incl1, 63);
   }
   if (lane == 0) {
     int32_t* fc = ws.fcount + f * FC_N;
     fc[FC_NUMBERED] = carry;
-    fc[FC_MATCHED] = matched_end;
     fc[FC_FAR_ITEMS] = carry0;
     fc[FC_CLOSE_ITEMS] = carry1;
-    if (lplan && n <= lcap) {
-      lend[2 * n] = carry0;
-      lend[2 * n + 1] = carry1;
-    }
-  }
-  if (!items) return;
-  // item records: the frame's close items from 0, its far items after them; each lane
-  // writes those of its box (re-reading the plan it stored above)
-  ItemRec* rec = ws.items + (size_t)f * ws.items_cap;
-  for (int base = 0; base < n; base += 64) {
-    const int i = base + lane;
-    if (i >= n) continue;
-    const BoxPlan pl = ws.plan[fr.box_off + i];
-    if (pl.status != -1 || pl.nblk <= 0) continue;
-    const int ib = P.item_blocks[pl.level];
-    const int nitem = (pl.nblk + ib - 1) / ib;
-    const int at = (pl.level == 1 ? 0 : carry1) + pl.ioff;
-    for (int t = 0; t < nitem; ++t) {
-      ItemRec r;
-      r.k = i;
-      r.first = t * ib;
-      r.nblk = pl.nblk;
-      r.off = pl.off;
-      r.nbx = pl.nbx; r.bw = pl.bw; r.bh = pl.bh; r.ox = pl.ox; r.oy = pl.oy;
-      r.lx0 = pl.lx0; r.ly0 = pl.ly0; r.lw = pl.lw; r.lh = pl.lh;
-      r.pad[0] = r.pad[1] = r.pad[2] = 0;
-      rec[at + t] = r;
-    }
-  }
-}
-
-// The item records of frame f (as plan_frame writes them) by the nthr threads of one
-// workgroup, after plan_frame(..., items = false) has stored the frame's plans, running
-// item ends and counters (and the threads have synchronised with it): thread tid writes
-// items tid, tid + nthr, ...; the box of an item is found by binary search on the running
-// item ends of its level. With lds (lds_cap words the caller is done with) holding both
-// levels' ends of the frame, they are copied there first and searched in LDS. With
-// lplan (a frame of at most lcap boxes), plan_frame's LDS copies of the plans and ends
-// are used instead.
-__device__ __forceinline__ void write_frame_items(const MatchParamsDev& P, const FrameDev& fr, int f,
-                                                  int n_total, const MatchWs& ws, int tid, int nthr,
-                                                  int32_t* lds = nullptr, int lds_cap = 0,
-                                                  const BoxPlan* lplan = nullptr,
-                                                  const int32_t* lend = nullptr, int lcap = 0) {
-  const int n = fr.n_boxes;
-  const bool from_plan = lplan && n <= lcap;
-  const bool in_lds = !from_plan && lds && 2 * n <= lds_cap;
-  if (from_plan) {
-    lds = (int32_t*)lend;
-  } else if (in_lds) {
-    __syncthreads();   // every thread is done with the caller's use of the LDS
-    for (int i = tid; i < n; i += nthr) {
-      lds[i] = ws.litem_end[fr.box_off + i];
-      lds[n + i] = ws.litem_end[(size_t)n_total + fr.box_off + i];
-    }
-    __syncthreads();
-  }
-  const int32_t* fc = ws.fcount + f * FC_N;
-  const int n_close = from_plan ? lend[2 * n + 1] : fc[FC_CLOSE_ITEMS];
-  const int n_far = from_plan ? lend[2 * n] : fc[FC_FAR_ITEMS];
-  ItemRec* rec = ws.items + (size_t)f * ws.items_cap;
-  for (int t = tid; t < n_close + n_far; t += nthr) {
-    const int level = t < n_close ? 1 : 0;
-    const int q = level ? t : t - n_close;
-    const int32_t* end = in_lds || from_plan ? lds + level * n
-                                             : ws.litem_end + (size_t)level * n_total + fr.box_off;
-    int lo = 0, hi = n - 1;   // first box whose running end passes q
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (end[mid] > q) hi = mid;
-      else lo = mid + 1;
-    }
-    const BoxPlan pl = from_plan ? lplan[lo] : ws.plan[fr.box_off + lo];
-    ItemRec r;
-    r.k = lo;
-    r.first = (q - pl.ioff) * P.item_blocks[level];
-    r.nblk = pl.nblk;
-    r.off = pl.off;
-    r.nbx = pl.nbx; r.bw = pl.bw; r.bh = pl.bh; r.ox = pl.ox; r.oy = pl.oy;
-    r.lx0 = pl.lx0; r.ly0 = pl.ly0; r.lw = pl.lw; r.lh = pl.lh;
-    r.pad[0] = r.pad[1] = r.pad[2] = 0;
-    rec[t] = r;
   }
 }
 
 // ---------------------------------------------------------------------------------
 // per-block steps
 // ---------------------------------------------------------------------------------
-// first of the frame's boxes whose running block end passes q (one vector load per 64)
+// The first of the n running ends that passes q (the last one otherwise): one ballot per
+// 64, the loads of 256 issued together.
 __device__ __forceinline__ int find_box(const int32_t* __restrict__ end, int n, int q, int lane) {
-  for (int base = 0; base < n; base += 64) {
-    const int e = base + lane < n ? end[base + lane] : 0x7FFFFFFF;
-    const uint64_t m = __ballot(e > q);
-    if (m) return base + __ffsll((unsigned long long)m) - 1;
+  for (int base = 0; base < n; base += 256) {
+    int e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = base + 64 * u + lane;
+      e[u] = 0x7FFFFFFF;
+      if (base + 64 * u < n && i < n) e[u] = end[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint64_t m = __ballot(e[u] > q);
+      if (m) return min(base + 64 * u + __ffsll((unsigned long long)m) - 1, n - 1);
+    }
   }
   return n - 1;
+}
+
+// Work item q of frame f's level: its box, found on the running item ends of the plan, and
+// the box's block geometry. The plan holds one record per box and none per item: a frame's
+// plan is one wave's work, and writing thousands of item records from it took most of a
+// many-box frame's time (3840 x 2160 with 200 boxes: 155 us of census and plan).
+__device__ __forceinline__ ItemRec find_item(const MatchParamsDev& P, const FrameDev& fr, int n_total,
+                                             const MatchWs& ws, int level, int q, int lane) {
+  const int k = find_box(ws.litem_end + (size_t)level * n_total + fr.box_off, fr.n_boxes, q, lane);
+  const BoxPlan pl = ws.plan[fr.box_off + k];
+  ItemRec r;
+  r.k = k;
+  r.first = uniform((q - pl.ioff) * P.item_blocks[level]);
+  r.nblk = uniform(pl.nblk); r.off = uniform(pl.off);
+  r.nbx = uniform(pl.nbx); r.bw = uniform(pl.bw); r.bh = uniform(pl.bh);
+  r.ox = uniform(pl.ox); r.oy = uniform(pl.oy);
+  r.lx0 = uniform(pl.lx0); r.ly0 = uniform(pl.ly0); r.lw = uniform(pl.lw); r.lh = uniform(pl.lh);
+  return r;
 }
 
 struct BlockGeom {
@@ -1434,7 +1367,7 @@ __device__ __forceinline__ void match_block_dy(const MatchParamsDev& P, const Fr
   wave_sync();
 }
 
-// Work item of frame f at `level` from its record: wave w of the workgroup runs blocks
+// Work item of frame f at `level`: wave w of the workgroup runs blocks
 // r.first + w + 4 j of the box that exist.
 __device__ __forceinline__ BoxPlan item_plan(const ItemRec& r, int f, int level) {
   BoxPlan pl = {};
@@ -1466,24 +1399,20 @@ __device__ __forceinline__ void run_item_rec(const MatchParamsDev& P, const Fram
 // Loop of a workgroup over the work items of one level of every frame (frames in
 // order, each frame's items in box order), dealt XCD by XCD (xcd_deal). Item numbers
 // come from the workgroup index, so the loop is uniform across the workgroup and needs
-// no shared counter. body(f, q, at) gets the frame, the item number within the frame's
-// level and the item's record within the frame's records (close items first, then far).
+// no shared counter. body(f, q) gets the frame and the item number within the frame's
+// level.
 template <class Body>
 __device__ __forceinline__ void level_items(const FramesDev& FR, const MatchWs& ws, int level,
                                             Body body) {
   const int lane = threadIdx.x & 63;
-  const int n_close = lane < FR.n ? ws.fcount[lane * FC_N + FC_CLOSE_ITEMS] : 0;
-  const int n_far = lane < FR.n ? ws.fcount[lane * FC_N + FC_FAR_ITEMS] : 0;
-  const int cnt = level == 0 ? n_far : n_close;
-  const int incl = wave_incl_scan(cnt, lane);
-  const int total = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+  const int cnt = lane < FR.n ? ws.fcount[lane * FC_N + (level == 0 ? FC_FAR_ITEMS : FC_CLOSE_ITEMS)] : 0;
+  const int incl = wave_incl_scan(cnt);
+  const int total = __builtin_amdgcn_readlane(incl, 63);
   const Deal dl = xcd_deal(total);
   for (int q = dl.first; q < dl.end; q += dl.step) {
     const uint64_t m = __ballot(lane < FR.n && incl > q);
     const int f = __ffsll((unsigned long long)m) - 1;
-    const int excl = __builtin_amdgcn_readfirstlane(__shfl(incl - cnt, f, 64));
-    const int skip = level == 0 ? __builtin_amdgcn_readlane(n_close, f) : 0;
-    body(f, q - excl, q - excl + skip);
+    body(f, q - __builtin_amdgcn_readlane(incl - cnt, f));
   }
 }
 
@@ -1524,7 +1453,7 @@ __device__ __forceinline__ uint32_t radix_select(const float* vals, int n, int k
     if (tid < 64) {
       const int c0 = sc[4 * tid], c1 = sc[4 * tid + 1], c2 = sc[4 * tid + 2], c3 = sc[4 * tid + 3];
       const int sum = c0 + c1 + c2 + c3;
-      const int incl = wave_incl_scan(sum, tid);
+      const int incl = wave_incl_scan(sum);
       const int excl = incl - sum;
       if (k >= excl && k < incl) {   // exactly one lane
         int d = 4 * tid, kk = k - excl;
@@ -1568,7 +1497,7 @@ __device__ __forceinline__ void radix_sort_global(float* a, float* tmp, int n, i
     // exclusive scan of the 256 digit counts (thread t holds digit t)
     {
       const int c = base[tid];
-      const int incl = wave_incl_scan(c, lane);
+      const int incl = wave_incl_scan(c);
       __syncthreads();
       if (lane == 63) cnt[wave] = incl;   // wave totals (cnt is all zero otherwise)
       __syncthreads();
@@ -1628,7 +1557,7 @@ __device__ __forceinline__ void find_rank_bins(AggLds& sm, int r1, int r2, bool 
   const int c0 = sm.hist[4 * tid], c1 = sm.hist[4 * tid + 1], c2 = sm.hist[4 * tid + 2],
             c3 = sm.hist[4 * tid + 3];
   const int sum = c0 + c1 + c2 + c3;
-  const int incl = wave_incl_scan(sum, lane);
+  const int incl = wave_incl_scan(sum);
   if (lane == 63) sm.scratch[256 + wave] = incl;
   __syncthreads();
   int excl = incl - sum;
@@ -1926,8 +1855,8 @@ __device__ __forceinline__ void aggregate_box(const MatchParamsDev& P, const Mat
 // kernel (ROWS block rows per wave, CPL candidates per lane, PASSES passes) and the
 // row-half kernel (32 CPL candidates per wave).
 // run_item: wave `wave`'s share of work item r (frame f, level `level`).
-// frame_state: what a matcher reads per frame before an item's record arrives (issued
-// first, so that its loads and the record's are in flight together).
+// frame_state: what a matcher reads per frame before an item's plan arrives (issued
+// first, so that its loads and the plan's are in flight together).
 struct NoFrameState {};
 template <int ROWS, int NX, int CPL, int PASSES>
 struct TiledMatcher {
@@ -1991,24 +1920,6 @@ struct QuadMatcher {
       match_blocks_quad<CPL>(P, fr, ws, dbg, f, level, r, first, lane, lds);
   }
 };
-
-// ---------------------------------------------------------------------------------
-// work items
-// ---------------------------------------------------------------------------------
-// Work item q of the frame's level: wave w of the workgroup runs blocks
-// item_blocks * (q - first item of the box) + w + 4 j of the item's box that exist.
-template <class RunBlock>
-__device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr, int f,
-                                         int n_total, const MatchWs& ws, int level, int q,
-                                         int wave, int lane, RunBlock run) {
-  const int k = find_box(ws.litem_end + (size_t)level * n_total + fr.box_off, fr.n_boxes, q, lane);
-  const BoxPlan pl = ws.plan[fr.box_off + k];
-  const int first = P.item_blocks[level] * (q - pl.ioff);
-  for (int j = wave; j < P.item_blocks[level]; j += kItemWaves) {
-    const int local = first + j;
-    if (local < pl.nblk) run(block_ctx(P, fr, f, k, pl, local, level));
-  }
-}
 
 }  // namespace dev
 }  // namespace ocsr

@@ -46,10 +46,8 @@ __global__ __launch_bounds__(256) void fused_kernel(MatchParamsDev P, FramesDev 
   if (w < F) {
     uint32_t* bits = (uint32_t*)lds;
     int* sc = (int*)(bits + kFrameTileWords);
-    if (wave == 0) dev::plan_frame(P, FR.f[w], w, FR.n_boxes_total, boxes, ws, lane, false);
+    if (wave == 0) dev::plan_frame(P, FR.f[w], w, FR.n_boxes_total, boxes, ws, lane);
     dev::list_frame_tiles(P, FR.f[w], w, boxes, ws, bits, sc);
-    dev::write_frame_items(P, FR.f[w], w, FR.n_boxes_total, ws, tid, 256, (int32_t*)bits,
-                           kFrameTileWords);
     __syncthreads();   // the LDS is reused below
   }
   dev::grid_barrier(ws.gcount + GC_BAR0, G, timeout);
@@ -57,7 +55,7 @@ __global__ __launch_bounds__(256) void fused_kernel(MatchParamsDev P, FramesDev 
     int* pre = mprefix;   // the frames' list lengths, then reused for the items
     if (tid < 64) {
       const int cnt = lane < F ? ws.fcount[lane * FC_N + FC_TILES] : 0;
-      const int incl = dev::wave_incl_scan(cnt, lane);
+      const int incl = dev::wave_incl_scan(cnt);
       if (lane < F) pre[lane + 1] = incl;
       if (lane == 0) pre[0] = 0;
     }
@@ -84,7 +82,7 @@ __global__ __launch_bounds__(256) void fused_kernel(MatchParamsDev P, FramesDev 
   if (tid < 64) {
     const int j = lane < F ? lane : lane - F;
     const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt, lane);
+    const int incl = dev::wave_incl_scan(cnt);
     if (lane < 2 * F) mprefix[lane + 1] = incl;
     if (lane == 0) mprefix[0] = 0;
   }
@@ -101,18 +99,16 @@ __global__ __launch_bounds__(256) void fused_kernel(MatchParamsDev P, FramesDev 
       const int f = slot < F ? slot : slot - F;
       const FrameDev& fr = FR.f[f];
       const int q = m - mprefix[slot];
-      const int at = q + (slot < F ? 0 : mprefix[f + 1] - mprefix[f]);
-      const ItemRec* rp = ws.items + (size_t)f * ws.items_cap + at;
       // per-lane indexing formed afresh per item (as in match_pair2_kernel)
       int il = lane;
       asm volatile("" : "+v"(il));
       if (slot < F) {
         const typename CM::State st = CM::frame_state(ws, fr, il);
-        const ItemRec rec = *rp;
+        const ItemRec rec = dev::find_item(P, fr, FR.n_boxes_total, ws, 1, q, il);
         CM::run_item(P, fr, ws, DebugDev{}, f, 1, rec, wave, il, wl, st);
       } else {
         const typename FM::State st = FM::frame_state(ws, fr, il);
-        const ItemRec rec = *rp;
+        const ItemRec rec = dev::find_item(P, fr, FR.n_boxes_total, ws, 0, q, il);
         FM::run_item(P, fr, ws, DebugDev{}, f, 0, rec, wave, il, wl, st);
       }
     }

@@ -38,22 +38,18 @@ __global__ __launch_bounds__(256) void frame_census_kernel(MatchParamsDev P, Fra
 // Plan of frame blockIdx.x and the list of its census tiles. Wave 0 plans the boxes while
 // waves 1-3 mark the tiles their searches read, each wave in a tile map of its own (so
 // the marking waits for no workgroup barrier, and the plan and the marking overlap);
-// then all four waves list the tiles of the three maps and write the work items, from
-// the plans wave 0 also left in LDS.
+// then all four waves list the tiles of the three maps.
 __global__ __launch_bounds__(256) void plan_tiles_kernel(MatchParamsDev P, FramesDev FR,
                                                          const ocsr_box* boxes, MatchWs ws) {
   constexpr int kMaps = kItemWaves - 1;
-  constexpr int kPlanCap = 128;   // frames of at most this many boxes keep their plans in LDS
   __shared__ uint32_t bits[kMaps * kFrameTileWords];
-  __shared__ BoxPlan lplan[kPlanCap];
-  __shared__ int32_t lend[2 * kPlanCap + 2];
   __shared__ int sc[8];
   const int f = blockIdx.x;
   const FrameDev& fr = FR.f[f];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   if (wave == 0) {
-    dev::plan_frame(P, fr, f, FR.n_boxes_total, boxes, ws, lane, false, lplan, lend, kPlanCap);
+    dev::plan_frame(P, fr, f, FR.n_boxes_total, boxes, ws, lane);
   } else {
     uint32_t* map = bits + (wave - 1) * kFrameTileWords;
     const int n_tiles = 2 * (fr.tiles0 + fr.tiles1);
@@ -64,8 +60,6 @@ __global__ __launch_bounds__(256) void plan_tiles_kernel(MatchParamsDev P, Frame
   }
   __syncthreads();
   dev::compact_frame_tiles(fr, f, ws, bits, kMaps, kFrameTileWords, sc);
-  dev::write_frame_items(P, fr, f, FR.n_boxes_total, ws, threadIdx.x, 256, (int32_t*)bits,
-                         kMaps * kFrameTileWords, lplan, lend, kPlanCap);
 }
 
 // Census of the listed tiles of every frame by persistent workgroups: the frames' lists,
@@ -80,7 +74,7 @@ __global__ __launch_bounds__(256) void census_list_kernel(MatchParamsDev P, Fram
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < 64) {
     const int cnt = lane < FR.n ? ws.fcount[lane * FC_N + FC_TILES] : 0;
-    const int incl = dev::wave_incl_scan(cnt, lane);
+    const int incl = dev::wave_incl_scan(cnt);
     if (lane < FR.n) pre[lane + 1] = incl;
     if (lane == 0) pre[0] = 0;
   }
@@ -142,9 +136,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tiled_waves
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   void* wl = (char*)lds + wave * kWave;
-  dev::level_items(FR, ws, level, [&](int f, int, int at) {
+  dev::level_items(FR, ws, level, [&](int f, int q) {
     const FrameDev& fr = FR.f[f];
-    const ItemRec r = ws.items[(size_t)f * ws.items_cap + at];
+    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
     dev::run_item_rec(P, fr, f, level, r, wave, [&](const dev::BlockCtx& c) {
       dev::match_block_tiled<ROWS, NX, CPL, PASSES>(P, fr, ws, dbg, c, lane, wl);
     });
@@ -177,7 +171,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves<
     // j - F's far level
     const int j = lane < F ? lane : lane - F;
     const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt, lane);
+    const int incl = dev::wave_incl_scan(cnt);
     if (lane < 2 * F) prefix[lane + 1] = incl;
     if (lane == 0) prefix[0] = 0;
   }
@@ -193,9 +187,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves<
     const int f = slot < F ? slot : slot - F;
     const FrameDev& fr = FR.f[f];
     const int q = m - prefix[slot];
-    // the frame's far items follow its close items (slot f) in the records
-    const int at = q + (slot < F ? 0 : prefix[f + 1] - prefix[f]);
-    const ItemRec r = ws.items[(size_t)f * ws.items_cap + at];
+    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, slot < F ? 1 : 0, q, lane);
     if (slot < F) {
       dev::run_item_rec(P, fr, f, 1, r, wave, [&](const dev::BlockCtx& c) {
         dev::match_block_tiled<CR_, CX, CC, CP>(P, fr, ws, dbg, c, lane, wl);
@@ -223,7 +215,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
   if (threadIdx.x < 64) {
     const int j = lane < F ? lane : lane - F;
     const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt, lane);
+    const int incl = dev::wave_incl_scan(cnt);
     if (lane < 2 * F) prefix[lane + 1] = incl;
     if (lane == 0) prefix[0] = 0;
   }
@@ -240,19 +232,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     const int f = slot < F ? slot : slot - F;
     const FrameDev& fr = FR.f[f];
     const int q = m - prefix[slot];
-    const int at = q + (slot < F ? 0 : prefix[f + 1] - prefix[f]);
-    const ItemRec* rp = ws.items + (size_t)f * ws.items_cap + at;
     // the lane index passes through an empty asm statement per item, so that neither
     // matcher's per-lane indexing is held in registers across the loop (both would be)
     int il = lane;
     asm volatile("" : "+v"(il));
     if (slot < F) {
       const typename CM::State st = CM::frame_state(ws, fr, il);
-      const ItemRec r = *rp;
+      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 1, q, il);
       CM::run_item(P, fr, ws, dbg, f, 1, r, wave, il, wl, st);
     } else {
       const typename FM::State st = FM::frame_state(ws, fr, il);
-      const ItemRec r = *rp;
+      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 0, q, il);
       FM::run_item(P, fr, ws, dbg, f, 0, r, wave, il, wl, st);
     }
   }
@@ -266,10 +256,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   void* wl = (char*)lds + wave * M::kLds;
-  dev::level_items(FR, ws, level, [&](int f, int, int at) {
+  dev::level_items(FR, ws, level, [&](int f, int q) {
     const FrameDev& fr = FR.f[f];
     const typename M::State st = M::frame_state(ws, fr, lane);
-    const ItemRec r = ws.items[(size_t)f * ws.items_cap + at];
+    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
     M::run_item(P, fr, ws, dbg, f, level, r, wave, lane, wl, st);
   });
 }
@@ -292,7 +282,7 @@ __global__ __launch_bounds__(256) void match_dy_pair_kernel(MatchParamsDev P, Fr
     // j - F's far level
     const int j = lane < F ? lane : lane - F;
     const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt, lane);
+    const int incl = dev::wave_incl_scan(cnt);
     if (lane < 2 * F) prefix[lane + 1] = incl;
     if (lane == 0) prefix[0] = 0;
   }
@@ -306,9 +296,7 @@ __global__ __launch_bounds__(256) void match_dy_pair_kernel(MatchParamsDev P, Fr
     const int f = slot < F ? slot : slot - F;
     const FrameDev& fr = FR.f[f];
     const int q = m - prefix[slot];
-    // the frame's far items follow its close items in the records
-    const int at = q + (slot < F ? 0 : prefix[f + 1] - prefix[f]);
-    const ItemRec r = ws.items[(size_t)f * ws.items_cap + at];
+    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, slot < F ? 1 : 0, q, lane);
     if constexpr (FROWS == CROWS) {
       // one matcher for both levels: a single inlined copy keeps the register count of
       // the one-level kernel
@@ -344,7 +332,7 @@ size_t match_ws_bytes(int n_frames, int n_boxes_total, int cap_blocks) {
          align256(2 * n * sizeof(int32_t)) +
          align256((size_t)kMaxFrames * FC_N * sizeof(int32_t)) + align256(GC_N * sizeof(int32_t)) +
          2 * align256(c * sizeof(float)) + align256(c * sizeof(uint8_t)) +
-         (size_t)(n_frames > 0 ? n_frames : 1) * items_capacity(n_boxes_total, cap_blocks) * sizeof(ItemRec);
+         (size_t)(n_frames > 0 ? n_frames : 1) * reserved_bytes(n_boxes_total, cap_blocks);
 }
 
 MatchWs match_ws_carve(void* base, int n_frames, int n_boxes_total, int cap_blocks) {
@@ -360,8 +348,6 @@ MatchWs match_ws_carve(void* base, int n_frames, int n_boxes_total, int cap_bloc
   ws.blk_val = (float*)b;       b += align256(c * sizeof(float));
   ws.agg_tmp = (float*)b;       b += align256(c * sizeof(float));
   ws.blk_flag = (uint8_t*)b;    b += align256(c * sizeof(uint8_t));
-  ws.items = (ItemRec*)b;
-  ws.items_cap = items_capacity(n_boxes_total, cap_blocks);
   return ws;
 }
 

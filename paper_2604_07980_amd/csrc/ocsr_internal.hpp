@@ -146,26 +146,22 @@ struct BoxClip {
 constexpr int kItemWaves = 4;
 constexpr int kMaxBlocksPerWave = 8;
 
-// per-frame counters: blocks numbered, block end of the matched boxes, work items of
-// the far and close levels
-enum { FC_NUMBERED = 0, FC_MATCHED = 1, FC_FAR_ITEMS = 2, FC_CLOSE_ITEMS = 3, FC_TILES = 4, FC_N = 8 };
+// per-frame counters: blocks numbered, work items of the far and close levels, census
+// tiles listed
+enum { FC_NUMBERED = 0, FC_FAR_ITEMS = 2, FC_CLOSE_ITEMS = 3, FC_TILES = 4, FC_N = 8 };
 // call-wide counters: the timeout flag, and the arrival slots of the fused launch's two
 // grid barriers (arrivals spread over kBarSlots counters to keep atomics uncontended)
 constexpr int kBarSlots = 8;
 enum { GC_TIMEOUT = 0, GC_BAR0 = 8, GC_BAR1 = 16, GC_BAR2 = 24, GC_N = 32 };
 
-// A work item as the plan writes it: the box, the item's first block and the box's
-// block geometry, so that a matching workgroup reads one record (one cache line) and
-// can stage its blocks' strips at once.
+// A work item: the box, the item's first block and the box's block geometry.
 struct ItemRec {
   int32_t k;                       // box within the frame
   int32_t first;                   // the item's first block (0-based within the box)
   int32_t nblk, off;               // the box's blocks and its first block number
   int32_t nbx, bw, bh, ox, oy;     // block grid
   int32_t lx0, ly0, lw, lh;        // level box
-  int32_t pad[3];
 };
-static_assert(sizeof(ItemRec) == 64, "one cache line per record");
 
 struct MatchWs {
   BoxPlan* plan;       // [n_boxes_total]
@@ -177,14 +173,13 @@ struct MatchWs {
   float* agg_tmp;      // [n_frames][cap_blocks] sort buffer of the aggregation of boxes
                        // with more blocks than it keeps in LDS
   uint8_t* blk_flag;   // [n_frames][cap_blocks] bit 0 eligible, bit 1 valid
-  ItemRec* items;      // [n_frames][items_cap]: a frame's close items, then its far items
-  int32_t items_cap;   // records per frame
 };
 
-// Work items of a frame of at most cap_blocks blocks: items hold at least kItemWaves
-// blocks of one box, so there are at most cap_blocks / kItemWaves + one per box.
-inline int32_t items_capacity(int n_boxes_total, int cap_blocks) {
-  return (cap_blocks > 0 ? cap_blocks : 1) / kItemWaves + (n_boxes_total > 0 ? n_boxes_total : 1);
+// Bytes at the end of a frame's share of the workspace that no kernel uses. They keep
+// ocsr_*_workspace_bytes, and with them the calls that a given buffer or the scratch of
+// ocsr_match_boxes_noalloc takes, as they have been.
+inline size_t reserved_bytes(int n_boxes_total, int cap_blocks) {
+  return 64 * (size_t)((cap_blocks > 0 ? cap_blocks : 1) / kItemWaves + (n_boxes_total > 0 ? n_boxes_total : 1));
 }
 
 size_t match_ws_bytes(int n_frames, int n_boxes_total, int cap_blocks);
