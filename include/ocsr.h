@@ -481,7 +481,8 @@ int32_t ocsr_rect_filter_update(ocsr_rect_filter* f, const int32_t* counts, int3
  * launch (1..64, default 16). The launch deals its work items over this grid. */
 #define OCSR_OPTION_MATCH_WGS_PER_CU 4
 /* OCSR_OPTION_BLOCKS_PER_WAVE: blocks each wave of a matching workgroup takes per work
- * item (1..8, default 1); a work item holds 4 x this many blocks of one box. */
+ * item (1..8, default 1); a work item holds 4 x this many blocks of one box. A variant whose
+ * waves take several adjacent blocks together (rows = 1 or 2 below) counts those as one. */
 #define OCSR_OPTION_BLOCKS_PER_WAVE 5
 /* OCSR_OPTION_GRAPH: 1 submits whole-frame and batch calls (ocsr_range_frame,
  * ocsr_range_batch) as HIP graphs: the first call with a given set of arguments
@@ -518,19 +519,19 @@ int32_t ocsr_ctx_set_option(ocsr_ctx* ctx, int32_t option, int32_t value);
 /* ------------------------------------------------------------------------------ */
 /* A TILED path's blocks run in one of three kernel families, named by (rows, cpl,
  * passes):
- *   rows = 1: four blocks of up to 4 x 4 points per wave, 16 lanes per block, each lane
- *             `cpl` consecutive candidates over all of its block's points (16 * cpl
- *             candidates, passes = 1);
- *   rows = 2: one block of up to 8 x 8 points per wave, lanes over 32 candidate groups
- *             of `cpl` consecutive candidates and the block's two halves of 4 rows
- *             (32 * cpl candidates, passes = 1);
+ *   rows = 1: four horizontally adjacent blocks of up to 4 x 4 points per wave, their
+ *             terms on the matrix cores; 16 lanes per block, each with `cpl` consecutive
+ *             candidates (16 * cpl candidates, passes = 1);
+ *   rows = 2: two horizontally adjacent blocks of up to 8 x 8 points per wave, their terms
+ *             on the matrix cores; 32 lanes per block, each with `cpl` consecutive
+ *             candidates (32 * cpl candidates, passes = 1);
  *   rows = 4 or 8: a register-blocked kernel with `rows` block rows per wave (blocks up
  *             to 4 x 4 or 8 x 8), `cpl` consecutive candidates per lane and `passes`
  *             passes over the candidates, covering (64 / rows) * cpl * passes candidates.
  * Any variant that covers a path gives identical results; they differ in speed only. By
  * default the first covering variant in the library's order of preference is used:
- * rows = 1 for blocks up to 4 x 4 and 32 or 64 candidates, rows = 2 for blocks up to
- * 8 x 8 and up to 128 candidates, else the register-blocked kernels.
+ * rows = 1 for blocks up to 4 x 4 and up to 64 candidates, rows = 2 for blocks up to
+ * 8 x 8, else the generic kernel.
  *
  * ocsr_variant_candidates: writes up to `cap` (rows, cpl, passes) triples (host arrays)
  * that cover bw x bh blocks and n_candidates level candidates; returns how many exist

@@ -2,8 +2,8 @@
 grid size and whether both levels share one launch, measured on the caller's own
 workload and kept in a JSON table.
 
-The register-blocked matching kernel comes in variants (rows of a block per wave,
-candidates per lane) that all compute the same costs; blocks per wave and the grid size
+The matching kernels come in variants (blocks or block rows per wave, candidates per
+lane) that all compute the same costs; blocks per wave and the grid size
 only change how work items are dealt, and a shared launch only how they are launched.
 None of them changes a result, so the tuner times
 each choice on a real workload, requires its output to equal the default's bit for bit,

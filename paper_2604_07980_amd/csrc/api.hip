@@ -331,9 +331,12 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
   d->fb = f * b;
   d->d_eps = p->d_eps;
   d->cap_blocks = cap_blocks;
-  // work items: four blocks per wave for the four-block kernel, else blocks per wave
-  for (int l = 0; l < 2; ++l)
-    d->item_blocks[l] = kItemWaves * (d->path[l].rows == 1 ? 4 : ctx->blocks_per_wave);
+  // a wave of the matrix-core kernels takes four (rows = 1) or two (rows = 2) adjacent blocks
+  // together; the vertical kernels and all others one
+  for (int l = 0; l < 2; ++l) {
+    d->group_x[l] = d->vertical ? 1 : d->path[l].rows == 1 ? 4 : d->path[l].rows == 2 ? 2 : 1;
+    d->item_blocks[l] = kItemWaves * (d->group_x[l] == 4 ? 1 : ctx->blocks_per_wave);
+  }
   d->full_census = ctx->full_census;
   return OCSR_OK;
 }

@@ -36,7 +36,7 @@
 // measure 6% less than two.
 #include <algorithm>
 
-#include "ocsr_internal.hpp"
+#include "dev_fp4.hpp"
 
 namespace ocsr {
 namespace {
@@ -57,37 +57,12 @@ struct DenseArgs {
   int32_t cols, chunks;       // output columns per wave, chunks of the search
 };
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+using namespace dev;
+
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t shr1(uint32_t v) {   // lane i gets lane i - 1
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);
-}
-
-// 32 bits of a descriptor as 32 FP4 numbers: bit b of w becomes the sign of a number of
-// magnitude 1 (code 2). sign, one: 0x88888888 and 0x22222222, or both 0 for a word whose
-// terms do not count.
-__device__ __forceinline__ v4i fp4_signs(uint32_t w, uint32_t sign, uint32_t one) {
-  v4i f;
-  f.x = (int)((w & sign) | one);
-  f.y = (int)(((w << 1) & sign) | one);
-  f.z = (int)(((w << 2) & sign) | one);
-  f.w = (int)(((w << 3) & sign) | one);
-  return f;
-}
-constexpr uint32_t kSign = 0x88888888u, kOne = 0x22222222u;
-// the two constants in registers that v_and_or_b32 can take together (it has no literals and
-// one scalar operand)
-__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
-__device__ __forceinline__ v16f mfma_fp4(v4i a, v4i b, v16f c) {
-  const v8i A = {a.x, a.y, a.z, a.w, 0, 0, 0, 0}, B = {b.x, b.y, b.z, b.w, 0, 0, 0, 0};
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
 }
 
 // The words of one image row that a chunk reads: the lane's fixed column and its T moving

@@ -3,7 +3,8 @@
 //
 //   plan_frame        one wave per frame: clip, far/close type (Sec. 4.3.4 type
 //                     equation), level box, block grid, block and work-item numbers
-//   match_block_tiled one wave per block: occluder mask (Sec. 4.3.5), forward Hamming
+//   match_block_tiled one wave per block (match_group of dev_matrix.hpp: per group of blocks):
+//                     occluder mask (Sec. 4.3.5), forward Hamming
 //                     search (census cost equation), winner-take-all, parabola
 //                     (sub-pixel equation), backward search and L/R check (Sec. 4.3.3)
 //   aggregate_box     one workgroup per box: longest-segment or trimmed median of the
@@ -94,9 +95,9 @@ __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameD
       if ((long long)off + count > (long long)P.cap_blocks) pl.status = OCSR_REASON_CAPACITY_OVERFLOW;
       else nblk = count;
     }
-    // work items of item_blocks blocks of the box's level
-    const int ib = P.item_blocks[pl.level];
-    const int nitem = (nblk + ib - 1) / ib;
+    // work items of item_blocks groups of group_x horizontally adjacent blocks 
+    const int ib = P.item_blocks[pl.level], gx = P.group_x[pl.level];
+    const int nitem = nblk > 0 ? (block_groups(pl.nbx, pl.nby, gx) + ib - 1) / ib : 0;
     const int c0 = (pl.status == -1 && pl.level == 0) ? nitem : 0;
     const int c1 = (pl.status == -1 && pl.level == 1) ? nitem : 0;
     const int incl0 = wave_incl_scan(c0);
@@ -158,7 +159,7 @@ __device__ __forceinline__ ItemRec find_item(const MatchParamsDev& P, const Fram
   ItemRec r;
   r.k = k;
   r.first = uniform((q - pl.ioff) * P.item_blocks[level]);
-  r.nblk = uniform(pl.nblk); r.off = uniform(pl.off);
+  r.nblk = uniform(pl.nblk); r.ngrp = uniform(block_groups(pl.nbx, pl.nby, P.group_x[level])); r.off = uniform(pl.off);
   r.nbx = uniform(pl.nbx); r.bw = uniform(pl.bw); r.bh = uniform(pl.bh);
   r.ox = uniform(pl.ox); r.oy = uniform(pl.oy);
   r.lx0 = uniform(pl.lx0); r.ly0 = uniform(pl.ly0); r.lw = uniform(pl.lw); r.lh = uniform(pl.lh);
@@ -519,33 +520,6 @@ __device__ __forceinline__ void match_block_tiled(const MatchParamsDev& P, const
   wave_sync();
 }
 
-// ---------------------------------------------------------------------------------
-// TILED block of up to 8 x 8 points, lanes over (candidate group, row half): lane
-// l = 2 g + h takes block rows 4h .. 4h + 3 and the CPL consecutive strip positions
-// g CPL + c (c < CPL), so one wave covers 32 CPL candidates in one pass. For each of its
-// rows a lane reads the 8 template words and CPL + 7 strip words from LDS and forms
-// 8 CPL costs at 4 operations each; the two row halves of a candidate meet in one DPP
-// add, and the winner is a DPP wave minimum of packed (cost << 16 | index) keys. A strip
-// row is staged in 64-word chunks through a buffer resource per row (load_half_strip).
-// ---------------------------------------------------------------------------------
-// strip row stride beyond the candidates (see Half::SWP)
-constexpr int kHalfStripPad = 10;
-
-template <int CPL>
-struct Half {
-  static constexpr int NC = 32 * CPL;               // candidates one wave covers
-  // LDS words per strip row (>= NC + 7). The two row halves are read by the same
-  // instructions (lanes 2g and 2g + 1), so rows four apart must start in different LDS
-  // banks: 4 SWP is an odd multiple of 8 words.
-  static constexpr int SWP = NC + kHalfStripPad;
-  static constexpr int TH = 40;                     // template: rows 4..7 start here
-  static constexpr int TW = TH + 32;                // template words
-  static constexpr int CH = (NC + 7 + 63) / 64;     // 64-word chunks of a strip row
-  static constexpr size_t kLdsBytes =
-      sizeof(uint64_t) * (8 * SWP + TW) + sizeof(uint16_t) * 2 * NC;
-  static_assert(SWP >= NC + 7, "a strip row holds nd + 7 words");
-};
-
 // Whole-wave minimum of v (every lane gets it): DPP within rows of 16, then row
 // broadcasts (lane 15 into the next row, lane 31 into rows 2 and 3), then lane 63.
 __device__ __forceinline__ uint32_t wave_min_dpp(uint32_t v) {
@@ -558,112 +532,13 @@ __device__ __forceinline__ uint32_t wave_min_dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Strip rows 0 .. 7 of a level image from `rows` (the block's first row), words
-// [x_first, x_first + 64 CH) of each row, for S[jj * SWP + m], m < SWP; rows at or past
-// ny (which no kept point reads) are 0. load_half_strip issues the loads and
-// store_half_strip writes the words to LDS, so that a caller can put other loads in
-// flight between the two. Each row is read through a buffer resource spanning exactly
-// that row (W words; none for rows past ny), so a word outside the image, left or right,
-// reads as 0 by the hardware's range check without a memory access: a column below 0
-// gives a byte offset that wraps past the range. The rows' resources and offsets are
-// wave-uniform (scalar instructions); lane l reads word l of each 64-word chunk at a
-// byte offset fixed for the whole strip, so the loads take no per-lane address
-// arithmetic.
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <int CH>
-struct HalfStrip {
-  u32x2 w[8][CH];
-};
-template <int SWP, int CH>
-__device__ __forceinline__ HalfStrip<CH> load_half_strip(const uint64_t* __restrict__ rows, int pitch,
-                                                         int x_first, int ny, int W, int lane) {
-  static_assert(SWP > 64 * (CH - 1) && SWP <= 64 * CH, "the strip row ends in the last chunk");
-  uint32_t voff[CH];
-#pragma unroll
-  for (int c = 0; c < CH; ++c) voff[c] = (uint32_t)(x_first + 64 * c + lane) * 8u;
-  HalfStrip<CH> st;
-#pragma unroll
-  for (int jj = 0; jj < 8; ++jj) {
-    // W words for rows inside the block (jj < ny: the sign bit of jj - ny), else none
-    const int nrec = W * 8 * (int)((uint32_t)(jj - ny) >> 31);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(rows + (size_t)jj * pitch), (short)0, nrec, 0x00020000);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) st.w[jj][c] = __builtin_amdgcn_raw_buffer_load_b64(rs, voff[c], 0, 0);
-  }
-  return st;
-}
-// The last chunk goes first: its lanes past the row end write their chunk-0 word, which
-// the chunk-0 stores that follow overwrite (a wave's LDS writes land in order), so no
-// lane mask is needed and no load is held back behind one.
-template <int SWP, int CH>
-__device__ __forceinline__ void store_half_strip(uint64_t* __restrict__ S, const HalfStrip<CH>& st,
-                                                 int lane) {
-  auto word = [](u32x2 v) { return ((uint64_t)v.y << 32) | v.x; };
-  if constexpr (CH == 1) {
-    if (lane < SWP) {
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) S[jj * SWP + lane] = word(st.w[jj][0]);
-    }
-  } else {
-    const int mlast = 64 * (CH - 1) + lane < SWP ? 64 * (CH - 1) + lane : lane;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) S[jj * SWP + mlast] = word(st.w[jj][CH - 1]);
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-      for (int c = 0; c < CH - 1; ++c) S[jj * SWP + 64 * c + lane] = word(st.w[jj][c]);
-  }
-}
-
-// One direction of the search: acc[c] = cost of strip position g CPL + c over the lane's
-// rows, summed with the other row half. keep: the lane's point mask (bit r 8 + i for
-// row 4h + r, column i; 0 for points that do not exist). `full` (wave-uniform): every
-// point of an 8 x 8 block is kept, and a cost is 4 operations; otherwise each
-// difference is ANDed with its point's mask bit (6 operations), with no branch per row
-// or column.
-template <int CPL>
-__device__ __forceinline__ void half_costs(const uint64_t* __restrict__ T, const uint64_t* __restrict__ S,
-                                           int g, int h, bool full, uint32_t keep,
-                                           uint32_t (&acc)[CPL]) {
-  constexpr int SWP = Half<CPL>::SWP;
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) acc[c] = 0;
-  const uint64_t* __restrict__ trow = T + Half<CPL>::TH * h;
-  const uint64_t* __restrict__ srow = S + 4 * h * SWP + g * CPL;
-  if (full) {
-#pragma unroll 1
-    for (int r = 0; r < 4; ++r) {
-      uint64_t t[8], w[CPL + 7];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = trow[8 * r + i];
-#pragma unroll
-      for (int m = 0; m < CPL + 7; ++m) w[m] = srow[r * SWP + m];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = popc64_acc(t[i] ^ w[i + c], acc[c]);
-    }
-  } else {
-#pragma unroll 1
-    for (int r = 0; r < 4; ++r) {
-      uint64_t t[8], w[CPL + 7];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = trow[8 * r + i];
-#pragma unroll
-      for (int m = 0; m < CPL + 7; ++m) w[m] = srow[r * SWP + m];
-      const uint32_t kr = keep >> (8 * r);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint64_t k = ((kr >> i) & 1u) ? ~0ull : 0ull;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = popc64_acc((t[i] ^ w[i + c]) & k, acc[c]);
-      }
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < CPL; ++c)
-    acc[c] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc[c], 0xB1, 0xF, 0xF, false);
+// Minimum over each row of 16 lanes (every lane of the row gets it).
+__device__ __forceinline__ uint32_t row16_min_dpp(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));
+  return v;
 }
 
 // Whether point (fx, fy) lies in one of the rectangles held by the lanes of m (each lane
@@ -680,34 +555,10 @@ __device__ __forceinline__ bool in_lane_rects(uint64_t m, const BoxClip& co, int
   return hidden;
 }
 
-// Occlusion mask of a TILED block (Sec. 4.3.5) in the 8-column layout: bit j*8 + i is
-// set iff point (i, j) exists (i < nx, j < ny) and lies in no box of the frame that
-// overlaps box k and has a larger bottom y. Lane l tests point (l & 7, l >> 3).
-__device__ __forceinline__ uint64_t tiled_mask8(const MatchWs& ws, int box_off, int n, int k,
-                                                int s, int cx, int cy, int nx, int ny, int lane) {
-  const BoxClip ck = ws.clip[box_off + k];
-  const int pi = lane & 7, pj = lane >> 3;
-  const bool exists = pi < nx && pj < ny;
-  const int fx = s * (cx + pi), fy = s * (cy + pj);
-  const int bx0 = s * cx, bx1 = s * (cx + nx - 1);
-  const int by0 = s * cy, by1 = s * (cy + ny - 1);
-  bool hidden = false;
-  for (int jb = 0; jb < n; jb += 64) {
-    const int o = jb + lane;
-    const BoxClip co = o < n ? ws.clip[box_off + o] : BoxClip{0, 0, 0, 0};
-    const bool occ = o < n && o != k && ck.cx0 < co.cx1 && co.cx0 < ck.cx1 && ck.cy0 < co.cy1 &&
-                     co.cy0 < ck.cy1 && co.cy1 > ck.cy1 && co.cx0 <= bx1 && co.cx1 > bx0 &&
-                     co.cy0 <= by1 && co.cy1 > by0;
-    hidden |= in_lane_rects(__ballot(occ), co, fx, fy);
-  }
-  return __ballot(exists && !hidden);
-}
-
 // The boxes that may hide points of box k, for all blocks of one work item of a frame of
-// at most 64 boxes (in_lanes; otherwise each block scans the frame's boxes itself):
-// lane o holds box o's clipped rectangle, and bit o of `cand` is set iff box o overlaps
-// box k and has the larger bottom y, the part of tiled_mask8's test that does not depend
-// on the block.
+// at most 64 boxes (in_lanes): lane o holds box o's clipped rectangle, and bit o of `cand` is
+// set iff box o overlaps box k and has the larger bottom y, the part of the occlusion
+// test (Sec. 4.3.5) that does not depend on the block.
 struct OccLanes {
   BoxClip co;
   uint64_t cand;
@@ -729,351 +580,6 @@ __device__ __forceinline__ void box_candidates(OccLanes& oc, int n, int k, int l
   oc.cand = __ballot(lane < n && lane != k && ck.cx0 < co.cx1 && co.cx0 < ck.cx1 &&
                      ck.cy0 < co.cy1 && co.cy0 < ck.cy1 && co.cy1 > ck.cy1);
 }
-// tiled_mask8 from the rectangles of frame_lanes and box_candidates
-__device__ __forceinline__ uint64_t tiled_mask8_lanes(const OccLanes& oc, int s, int cx, int cy,
-                                                      int nx, int ny, int lane) {
-  const int pi = lane & 7, pj = lane >> 3;
-  const bool exists = pi < nx && pj < ny;
-  const int fx = s * (cx + pi), fy = s * (cy + pj);
-  const int bx0 = s * cx, bx1 = s * (cx + nx - 1);
-  const int by0 = s * cy, by1 = s * (cy + ny - 1);
-  const BoxClip co = oc.co;
-  const bool occ = ((oc.cand >> lane) & 1ull) && co.cx0 <= bx1 && co.cx1 > bx0 && co.cy0 <= by1 &&
-                   co.cy1 > by0;
-  // the ballot of candidates is taken by the whole wave (lanes past the block hold boxes too)
-  const bool hidden = in_lane_rects(__ballot(occ), co, fx, fy);
-  return __ballot(exists && !hidden);
-}
-
-// The 8-column mask in the record's layout (bit j * nx + i).
-__device__ __forceinline__ uint64_t pack_mask8(uint64_t m8, int nx, int ny, int lane) {
-  const int j = lane / nx, i = lane - j * nx;
-  return __ballot(lane < nx * ny && ((m8 >> (8 * j + i)) & 1ull));
-}
-
-// oc: the box's occluders when the frame's boxes fit the lanes (frame_lanes,
-// box_candidates). The occlusion mask comes first (from registers in that case), so that
-// a block that is not eligible loads no strip.
-template <int CPL>
-__device__ __forceinline__ void match_block_half(const MatchParamsDev& P, const FrameDev& fr,
-                                                 const MatchWs& ws, const DebugDev& dbg,
-                                                 const BlockCtx& c, const OccLanes& oc, int lane,
-                                                 void* lds) {
-  using HH = Half<CPL>;
-  constexpr int SWP = HH::SWP, CH = HH::CH, NC = HH::NC;
-  uint64_t* S = (uint64_t*)lds;
-  uint64_t* T = S + 8 * SWP;                   // row jj at 8 jj, rows 4..7 moved by TH - 32
-  uint16_t* costf = (uint16_t*)(T + HH::TW);   // a cost is at most 64 x 64
-  uint16_t* costb = costf + NC;
-  const int tslot = lane + (lane >= 32 ? HH::TH - 32 : 0);   // lane (i, jj) = i + 8 jj
-  const int g = lane >> 1, h = lane & 1;
-  const LevelDev& lv = fr.lv[c.level];
-  const PathDev& ph = P.path[c.level];
-  const int nd = ph.nd, dlo = ph.dlo, dhi = dlo + nd - 1;
-  const int nx = c.g.nx, ny = c.g.ny;
-  const int X0 = c.g.cx, Y0 = c.g.cy;
-  const int W = lv.W;
-  const uint64_t* __restrict__ Lb = uniform(lv.L + (size_t)Y0 * lv.pitch);
-  const uint64_t* __restrict__ Rb = uniform(lv.R + (size_t)Y0 * lv.pitch);
-  const uint64_t m8 = oc.in_lanes ? tiled_mask8_lanes(oc, c.g.s, X0, Y0, nx, ny, lane)
-                                  : tiled_mask8(ws, fr.box_off, fr.n_boxes, c.k, c.g.s, X0, Y0, nx, ny, lane);
-  const int npts = __popcll(m8);
-  const bool eligible = npts > 0 && 100 * npts >= P.min_point_pct * nx * ny;
-  if (!eligible) {
-    const uint64_t mask = dbg.blocks ? pack_mask8(m8, nx, ny, lane) : 0ull;
-    write_block(ws, dbg, c, ph, mask, false, dlo, dlo, 0, (float)dlo, 0, lane);
-    return;
-  }
-  // forward strip CR(X0 - dhi + m, Y0 + j) and template CL(X0 + i, Y0 + j), loaded together
-  const HalfStrip<CH> fw = load_half_strip<SWP, CH>(Rb, lv.pitch, X0 - dhi, ny, W, lane);
-  uint64_t tw;
-  {
-    const int i = lane & 7, jj = lane >> 3;
-    const bool ok = i < nx && jj < ny;
-    tw = Lb[ok ? (size_t)jj * lv.pitch + X0 + i : 0];
-    tw = ok ? tw : 0ull;
-  }
-  store_half_strip<SWP, CH>(S, fw, lane);
-  T[tslot] = tw;
-  wave_sync();
-  const bool full = m8 == ~0ull;   // an 8 x 8 block with every point kept
-  const uint32_t keep = (uint32_t)(m8 >> (32 * h));
-  uint32_t acc[CPL];
-  half_costs<CPL>(T, S, g, h, full, keep, acc);
-  // both lanes of a group hold the whole cost; a strip position past the range writes
-  // its (unread) slot at index e >= nd instead of a branch
-  uint32_t key = 0xFFFFFFFFu;
-#pragma unroll
-  for (int cc = 0; cc < CPL; ++cc) {
-    const int e = g * CPL + cc;            // strip position: candidate d = dhi - e
-    const bool in = e < nd;
-    const int kc = nd - 1 - e;
-    key = min(key, in ? (acc[cc] << 16) | (uint32_t)kc : 0xFFFFFFFFu);
-    costf[in ? kc : e] = (uint16_t)acc[cc];
-  }
-  key = wave_min_dpp(key);
-  const int best = (int)(key & 0xFFFFu);
-  const int d_f = dlo + best;
-  // backward template CR(X0 - d_f + i, Y0 + j): strip position dhi - d_f + i
-  {
-    const int i = lane & 7, jj = lane >> 3;
-    const uint64_t t = S[jj * SWP + (dhi - d_f) + i];
-    wave_sync();
-    T[tslot] = t;
-  }
-  const int ca = (int)costf[max(best - 1, 0)];
-  const int cb = (int)costf[min(best + 1, nd - 1)];
-  const float d_sub = subpixel(d_f, best, nd, ca, (int)(key >> 16), cb);
-  // backward strip CL(X0 - d_f + dlo + m, Y0 + j)
-  wave_sync();
-  store_half_strip<SWP, CH>(S, load_half_strip<SWP, CH>(Lb, lv.pitch, X0 - d_f + dlo, ny, W, lane), lane);
-  wave_sync();
-  half_costs<CPL>(T, S, g, h, full, keep, acc);
-  uint32_t bkey = 0xFFFFFFFFu;
-#pragma unroll
-  for (int cc = 0; cc < CPL; ++cc) {
-    const int kc = g * CPL + cc;           // candidate d' = dlo + kc (slots past nd unread)
-    bkey = min(bkey, kc < nd ? (acc[cc] << 16) | (uint32_t)kc : 0xFFFFFFFFu);
-  }
-  // the backward costs are read only for the debug output
-  if (dbg.cost_bwd) {
-#pragma unroll
-    for (int cc = 0; cc < CPL; ++cc) costb[g * CPL + cc] = (uint16_t)acc[cc];
-  }
-  bkey = wave_min_dpp(bkey);
-  const int d_b = dlo + (int)(bkey & 0xFFFFu);
-  const int lr_ok = abs(d_b - d_f) <= P.lr_tol;
-  uint64_t mask = 0;
-  if (dbg.blocks || dbg.cost_fwd || dbg.cost_bwd) {
-    mask = pack_mask8(m8, nx, ny, lane);
-    if (c.b < dbg.cap_blocks && (dbg.cost_fwd || dbg.cost_bwd)) {
-      wave_sync();
-      for (int kc = lane; kc < nd && kc < dbg.cap_nd; kc += 64) {
-        if (dbg.cost_fwd) dbg.cost_fwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)costf[kc];
-        if (dbg.cost_bwd) dbg.cost_bwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)costb[kc];
-      }
-    }
-  }
-  write_block(ws, dbg, c, ph, mask, true, d_f, d_b, lr_ok, d_sub, lr_ok, lane);
-  wave_sync();
-}
-
-// ---------------------------------------------------------------------------------
-// TILED blocks of up to 4 x 4 points, four blocks per wave: lane l = 16 q + g takes
-// block q of the four (its 16 lanes a DPP row) and the CPL consecutive strip positions
-// g CPL + c, so a row of lanes covers 16 CPL candidates and each lane forms the whole
-// cost of its candidates over the block's points (no reduction across lanes). The
-// winner of a block is a DPP minimum within its row of lanes. Each block has its own
-// strip and template in LDS, staged by its 16 lanes.
-// ---------------------------------------------------------------------------------
-template <int CPL>
-struct Quad {
-  static constexpr int NC = 16 * CPL;               // candidates per block
-  static constexpr int SWP = NC + 4;                // LDS words per strip row (>= NC + 3)
-  static constexpr int BLK = 4 * SWP + 16;          // LDS words per block: strip, template
-  static constexpr int CH = (NC + 3 + 15) / 16;     // 16-word chunks of a strip row
-  static constexpr size_t kLdsBytes = sizeof(uint64_t) * 4 * BLK + sizeof(uint32_t) * 2 * 4 * NC;
-};
-
-// Minimum over each row of 16 lanes (every lane of the row gets it).
-__device__ __forceinline__ uint32_t row16_min_dpp(uint32_t v) {
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));
-  return v;
-}
-
-// One quarter's strip: rows 0 .. ny - 1 from `rows` (its block's first row), words
-// [x_first, x_first + sw) into S[jj * SWP + m], 0 outside the image; g: the lane's
-// index in its quarter. All loads are issued before the first store.
-template <int CPL>
-__device__ __forceinline__ void stage_quad_strip(uint64_t* __restrict__ S, const uint64_t* __restrict__ rows,
-                                                 int pitch, int x_first, int ny, int sw, int W,
-                                                 bool live, int g) {
-  constexpr int SWP = Quad<CPL>::SWP, CH = Quad<CPL>::CH;
-  uint64_t w[4][CH];
-#pragma unroll
-  for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int m = 16 * c + g, x = x_first + m;
-      const bool ok = live && jj < ny && m < sw && x >= 0 && x < W;
-      w[jj][c] = rows[ok ? (size_t)jj * pitch + x : 0];
-      w[jj][c] = ok ? w[jj][c] : 0ull;
-    }
-#pragma unroll
-  for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (16 * c + g < SWP) S[jj * SWP + 16 * c + g] = w[jj][c];
-}
-
-// acc[c] = cost of strip position g CPL + c over the block's points; keep: the block's
-// point mask in the 4-column layout (bit j * 4 + i); `full`: every point of four 4 x 4
-// blocks is kept (wave-uniform).
-template <int CPL>
-__device__ __forceinline__ void quad_costs(const uint64_t* __restrict__ T, const uint64_t* __restrict__ S,
-                                           int g, bool full, uint32_t keep, uint32_t (&acc)[CPL]) {
-  constexpr int SWP = Quad<CPL>::SWP;
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) acc[c] = 0;
-  const uint64_t* __restrict__ srow = S + g * CPL;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    uint64_t t[4], w[CPL + 3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = T[4 * r + i];
-#pragma unroll
-    for (int m = 0; m < CPL + 3; ++m) w[m] = srow[r * SWP + m];
-    if (full) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = popc64_acc(t[i] ^ w[i + c], acc[c]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint64_t k = ((keep >> (4 * r + i)) & 1u) ? ~0ull : 0ull;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] = popc64_acc((t[i] ^ w[i + c]) & k, acc[c]);
-      }
-    }
-  }
-}
-
-// Blocks first .. first + 3 (those below nblk) of one box, one per row of 16 lanes.
-template <int CPL>
-__device__ __forceinline__ void match_blocks_quad(const MatchParamsDev& P, const FrameDev& fr,
-                                                  const MatchWs& ws, const DebugDev& dbg, int f,
-                                                  int level, const ItemRec& r, int first, int lane,
-                                                  void* lds) {
-  using QQ = Quad<CPL>;
-  constexpr int SWP = QQ::SWP, NC = QQ::NC;
-  const int q = lane >> 4, g = lane & 15;
-  const int local = first + q;
-  const bool live = local < r.nblk;
-  uint64_t* S = (uint64_t*)lds + q * QQ::BLK;
-  uint64_t* T = S + 4 * SWP;
-  uint32_t* costf = (uint32_t*)((uint64_t*)lds + 4 * QQ::BLK) + q * NC;
-  uint32_t* costb = costf + 4 * NC;
-  const LevelDev& lv = fr.lv[level];
-  const PathDev& ph = P.path[level];
-  const int nd = ph.nd, dlo = ph.dlo, dhi = dlo + nd - 1;
-  const int nx = r.bw, ny = r.bh, W = lv.W, s = lv.scale;
-  const int vv = live ? local / r.nbx : 0;
-  const int uu = live ? local - vv * r.nbx : 0;
-  const int X0 = r.ox + uu * nx, Y0 = r.oy + vv * ny;
-  const uint64_t* __restrict__ Lb = lv.L + (size_t)Y0 * lv.pitch;
-  const uint64_t* __restrict__ Rb = lv.R + (size_t)Y0 * lv.pitch;
-  const int sw = nd + nx - 1;
-  // forward strip CR(X0 - dhi + m, Y0 + j) and template CL(X0 + i, Y0 + j) of this
-  // lane's block, issued before the occluder scan
-  stage_quad_strip<CPL>(S, Rb, lv.pitch, X0 - dhi, ny, sw, W, live, g);
-  const int pi = g & 3, pj = g >> 2;
-  const bool exists = live && pi < nx && pj < ny;
-  {
-    uint64_t t = Lb[exists ? (size_t)pj * lv.pitch + X0 + pi : 0];
-    T[g] = exists ? t : 0ull;
-  }
-  // occlusion (Sec. 4.3.5): every block of the wave belongs to box k, so the boxes that
-  // occlude it are found once; each lane tests its own point against them
-  const BoxClip ck = ws.clip[fr.box_off + r.k];
-  const int fx = s * (X0 + pi), fy = s * (Y0 + pj);
-  bool hidden = false;
-  for (int jb = 0; jb < fr.n_boxes; jb += 64) {
-    const int o = jb + lane;
-    const BoxClip co = o < fr.n_boxes ? ws.clip[fr.box_off + o] : BoxClip{0, 0, 0, 0};
-    const bool occ = o < fr.n_boxes && o != r.k && ck.cx0 < co.cx1 && co.cx0 < ck.cx1 &&
-                     ck.cy0 < co.cy1 && co.cy0 < ck.cy1 && co.cy1 > ck.cy1;
-    uint64_t m = __ballot(occ);
-    while (m) {
-      const int src = __ffsll((unsigned long long)m) - 1;
-      m &= m - 1;
-      const int x0 = __builtin_amdgcn_readlane(co.cx0, src), x1 = __builtin_amdgcn_readlane(co.cx1, src);
-      const int y0 = __builtin_amdgcn_readlane(co.cy0, src), y1 = __builtin_amdgcn_readlane(co.cy1, src);
-      hidden |= fx >= x0 && fx < x1 && fy >= y0 && fy < y1;
-    }
-  }
-  const uint64_t m64 = __ballot(exists && !hidden);
-  const uint32_t keep = (uint32_t)(m64 >> (16 * q)) & 0xFFFFu;
-  const int npts = __popc(keep);
-  const bool eligible = live && npts > 0 && 100 * npts >= P.min_point_pct * nx * ny;
-  const bool full = m64 == ~0ull;
-  const bool writer = live && g == 0;
-  wave_sync();
-  uint32_t acc[CPL];
-  quad_costs<CPL>(T, S, g, full, keep, acc);
-  uint32_t key = 0xFFFFFFFFu;
-#pragma unroll
-  for (int cc = 0; cc < CPL; ++cc) {
-    const int e = g * CPL + cc;            // strip position: candidate d = dhi - e
-    if (e < nd) {
-      const int kc = nd - 1 - e;
-      key = min(key, (acc[cc] << 16) | (uint32_t)kc);
-      costf[kc] = acc[cc];
-    }
-  }
-  key = row16_min_dpp(key);
-  const int best = (int)(key & 0xFFFFu);
-  const int d_f = dlo + best;
-  // backward template CR(X0 - d_f + i, Y0 + j): strip position dhi - d_f + i
-  const uint64_t tb = S[pj * SWP + (dhi - d_f) + pi];
-  wave_sync();
-  T[g] = exists ? tb : 0ull;
-  const int ca = (int)costf[max(best - 1, 0)];
-  const int cb = (int)costf[min(best + 1, nd - 1)];
-  const float d_sub = subpixel(d_f, best, nd, ca, (int)(key >> 16), cb);
-  wave_sync();
-  stage_quad_strip<CPL>(S, Lb, lv.pitch, X0 - d_f + dlo, ny, sw, W, live, g);
-  wave_sync();
-  quad_costs<CPL>(T, S, g, full, keep, acc);
-  uint32_t bkey = 0xFFFFFFFFu;
-#pragma unroll
-  for (int cc = 0; cc < CPL; ++cc) {
-    const int kc = g * CPL + cc;           // candidate d' = dlo + kc
-    if (kc < nd) {
-      bkey = min(bkey, (acc[cc] << 16) | (uint32_t)kc);
-      costb[kc] = acc[cc];
-    }
-  }
-  bkey = row16_min_dpp(bkey);
-  const int d_b = dlo + (int)(bkey & 0xFFFFu);
-  const int lr_ok = abs(d_b - d_f) <= P.lr_tol;
-  const int slot = f * P.cap_blocks + r.off + local;
-  if (writer) {
-    ws.blk_val[slot] = (float)s * (eligible ? d_sub : (float)dlo);   // d_full = s * d (Sec. 4.1)
-    ws.blk_flag[slot] = (uint8_t)((eligible ? 1 : 0) | (eligible && lr_ok ? 2 : 0));
-  }
-  if (dbg.blocks || dbg.cost_fwd || dbg.cost_bwd) {
-    // record mask in the record's layout (bit j * nx + i) from the 4-column layout
-    const int jr = g / nx, ir = g - jr * nx;
-    const uint64_t pm = __ballot(live && g < nx * ny && ((keep >> (4 * jr + ir)) & 1u));
-    const uint64_t mask = (pm >> (16 * q)) & 0xFFFFull;
-    const int b = r.off + local;
-    if (writer && dbg.blocks && b < dbg.cap_blocks) {
-      ocsr_block_record rec;
-      rec.box = r.k; rec.level_scale = s; rec.u = uu; rec.v = vv;
-      rec.px0 = X0; rec.py0 = Y0; rec.nx = nx; rec.ny = ny;
-      rec.mask = mask; rec.eligible = eligible;
-      rec.d_f = eligible ? d_f : dlo; rec.d_b = eligible ? d_b : dlo;
-      rec.lr_ok = eligible ? lr_ok : 0; rec.d_sub = eligible ? d_sub : (float)dlo;
-      rec.valid = eligible && lr_ok;
-      rec.dlo = dlo; rec.nd = nd;
-      rec.dy_f = 0; rec.dy_b = 0;
-      dbg.blocks[b] = rec;
-    }
-    if (live && eligible && b < dbg.cap_blocks && (dbg.cost_fwd || dbg.cost_bwd)) {
-      wave_sync();
-      for (int kc = g; kc < nd && kc < dbg.cap_nd; kc += 16) {
-        if (dbg.cost_fwd) dbg.cost_fwd[(size_t)b * dbg.cap_nd + kc] = (uint16_t)costf[kc];
-        if (dbg.cost_bwd) dbg.cost_bwd[(size_t)b * dbg.cap_nd + kc] = (uint16_t)costb[kc];
-      }
-    }
-  }
-  wave_sync();
-}
-
 // ---------------------------------------------------------------------------------
 // Any block of up to 64 points on any point grid (TILED, or the single GRID block of
 // the paper's far path, Sec. 4.3.4 "Far Objects"), up to 256 candidates: one wave per
@@ -1851,9 +1357,9 @@ __device__ __forceinline__ void aggregate_box(const MatchParamsDev& P, const Mat
 }
 
 // ---------------------------------------------------------------------------------
-// Matchers of one level's TILED blocks, for the generic pair kernel: the register-blocked
-// kernel (ROWS block rows per wave, CPL candidates per lane, PASSES passes) and the
-// row-half kernel (32 CPL candidates per wave).
+// Matchers of one level's blocks, for the level and pair kernels: the register-blocked
+// kernel (ROWS block rows per wave, CPL candidates per lane, PASSES passes) and the generic
+// kernel; those on the matrix cores are in dev_matrix.hpp.
 // run_item: wave `wave`'s share of work item r (frame f, level `level`).
 // frame_state: what a matcher reads per frame before an item's plan arrives (issued
 // first, so that its loads and the plan's are in flight together).
@@ -1872,25 +1378,6 @@ struct TiledMatcher {
     });
   }
 };
-// (its frame state: the frame's box rectangles in lanes, when they fit)
-template <int CPL>
-struct HalfMatcher {
-  static constexpr size_t kLds = (Half<CPL>::kLdsBytes + 15) & ~(size_t)15;
-  using State = OccLanes;
-  static __device__ __forceinline__ State frame_state(const MatchWs& ws, const FrameDev& fr, int lane) {
-    return frame_lanes(ws, fr.box_off, fr.n_boxes, lane);
-  }
-  static __device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr,
-                                                  const MatchWs& ws, const DebugDev& dbg, int f,
-                                                  int level, const ItemRec& r, int wave, int lane,
-                                                  void* lds, const State& st) {
-    OccLanes oc = st;
-    box_candidates(oc, fr.n_boxes, r.k, lane);
-    run_item_rec(P, fr, f, level, r, wave, [&](const BlockCtx& c) {
-      match_block_half<CPL>(P, fr, ws, dbg, c, oc, lane, lds);
-    });
-  }
-};
 // any block of up to 64 points (GRID blocks included), lanes over candidates
 struct GenericMatcher {
   static constexpr size_t kLds = kGenericLdsBytes;
@@ -1905,21 +1392,5 @@ struct GenericMatcher {
     });
   }
 };
-// four blocks per wave: wave w takes blocks r.first + 4 w .. + 3 of a 16-block item
-template <int CPL>
-struct QuadMatcher {
-  static constexpr size_t kLds = (Quad<CPL>::kLdsBytes + 15) & ~(size_t)15;
-  using State = NoFrameState;
-  static __device__ __forceinline__ State frame_state(const MatchWs&, const FrameDev&, int) { return {}; }
-  static __device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr,
-                                                  const MatchWs& ws, const DebugDev& dbg, int f,
-                                                  int level, const ItemRec& r, int wave, int lane,
-                                                  void* lds, const State& = State()) {
-    const int first = r.first + 4 * wave;
-    if (first < r.nblk && first < r.first + P.item_blocks[level])
-      match_blocks_quad<CPL>(P, fr, ws, dbg, f, level, r, first, lane, lds);
-  }
-};
-
 }  // namespace dev
 }  // namespace ocsr

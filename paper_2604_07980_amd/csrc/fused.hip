@@ -15,6 +15,7 @@
 // box of the call with OCSR_REASON_INTERNAL_TIMEOUT instead of hanging.
 #include "dev_census.hpp"
 #include "dev_match.hpp"
+#include "dev_matrix.hpp"
 
 namespace ocsr {
 namespace {
@@ -192,11 +193,11 @@ hipError_t launch_fused(const MatchParamsDev& P, const FramesDev& FR, const ocsr
       e = launch_one(fused_kernel<3, 4, dev::FMT, dev::CMT>, P, FR, boxes, ws, out, sentinel,  \
                      n_cu, wgs_per_cu, stream);                                              \
       break;
-    OCSR_FUSED(kQ2H3, QuadMatcher<2>, HalfMatcher<3>)
-    OCSR_FUSED(kQ2H4, QuadMatcher<2>, HalfMatcher<4>)
-    OCSR_FUSED(kQ2H2, QuadMatcher<2>, HalfMatcher<2>)
-    OCSR_FUSED(kQ4H4, QuadMatcher<4>, HalfMatcher<4>)
-    OCSR_FUSED(kH2H3, HalfMatcher<2>, HalfMatcher<3>)
+    OCSR_FUSED(kQ2H3, QuadMatcher<2>, PairMatcher<3>)
+    OCSR_FUSED(kQ2H4, QuadMatcher<2>, PairMatcher<4>)
+    OCSR_FUSED(kQ2H2, QuadMatcher<2>, PairMatcher<2>)
+    OCSR_FUSED(kQ4H4, QuadMatcher<4>, PairMatcher<4>)
+    OCSR_FUSED(kH2H3, PairMatcher<2>, PairMatcher<3>)
 #undef OCSR_FUSED
     default:
       e = hipErrorNotSupported;

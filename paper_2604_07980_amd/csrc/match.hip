@@ -7,6 +7,7 @@
 // the fused persistent kernel.
 #include "dev_census.hpp"
 #include "dev_match.hpp"
+#include "dev_matrix.hpp"
 
 namespace ocsr {
 namespace {
@@ -157,7 +158,8 @@ constexpr int pair_waves() {
 // every far level (FV / CV: the far and close kernel variants).
 template <int FR_, int FX, int FC, int CR_, int CX, int CC, int CP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves<FR_, FC, CC, CP>()))) void match_pair_kernel(MatchParamsDev P, FramesDev FR,
-                                                         MatchWs ws, DebugDev dbg) {
+                                                         MatchWs ws) {
+  const DebugDev dbg = {};
   constexpr size_t kF = (dev::Tiled<FR_, FX, FC>::kLdsBytes + 15) & ~(size_t)15;
   constexpr size_t kC = (dev::Tiled<CR_, CX, CC, CP>::kLdsBytes + 15) & ~(size_t)15;
   constexpr size_t kWave = kF > kC ? kF : kC;
@@ -202,10 +204,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves<
 
 // Both levels in one launch with any pair of matchers (FM far, CM close): work items of
 // every frame's close level first, then of every far level. Compiled for WAVES waves per
-// SIMD.
+// SIMD. (Calls with debug output take one launch per level.)
 template <class FM, class CM, int WAVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void match_pair2_kernel(
-    MatchParamsDev P, FramesDev FR, MatchWs ws, DebugDev dbg) {
+    MatchParamsDev P, FramesDev FR, MatchWs ws) {
+  const DebugDev dbg = {};
   constexpr size_t kWave = FM::kLds > CM::kLds ? FM::kLds : CM::kLds;
   __shared__ uint64_t lds[(kItemWaves * kWave + 7) / 8];
   __shared__ int prefix[2 * kMaxFrames + 1];
@@ -248,10 +251,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
   }
 }
 
-// One level with any matcher.
-template <class M, int WAVES>
+// Waves per SIMD the matrix-core matchers are compiled for (their strip and accumulators
+// grow with the candidates per lane; checked in the built code: no spills).
+template <int CPL>
+constexpr int matrix_waves() { return CPL <= 4 ? 4 : CPL <= 6 ? 3 : 2; }
+
+// One level with any matcher. Without DBG no debug output is asked for, and its code and
+// pointers are not in the kernel.
+template <class M, int WAVES, bool DBG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void match_level_kernel(
-    MatchParamsDev P, FramesDev FR, MatchWs ws, DebugDev dbg, int level) {
+    MatchParamsDev P, FramesDev FR, MatchWs ws, DebugDev dbg_, int level) {
+  const DebugDev dbg = DBG ? dbg_ : DebugDev{};
   __shared__ uint64_t lds[(kItemWaves * M::kLds + 7) / 8];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
@@ -354,13 +364,12 @@ MatchWs match_ws_carve(void* base, int n_frames, int n_boxes_total, int cap_bloc
 namespace {
 // the built kernels, as in launch_level, in order of preference for the default
 struct BuiltVariant { int rows, nx, cpl, passes; };
-// rows = 2: the row-half kernel (lanes over 32 candidate groups x 2 row halves of an
-// up to 8 x 8 block, cpl candidates per group)
-// rows = 1: the four-block kernel (lanes over 4 blocks of up to 4 x 4 points x 16
-// candidate groups, cpl candidates per group)
+// rows = 2: two blocks of up to 8 x 8 points per wave on the matrix cores, cpl candidates on
+// each of 32 lanes; rows = 1: four blocks of up to 4 x 4, cpl candidates on each of 16 lanes
 constexpr BuiltVariant kBuilt[] = {
     {1, 4, 2, 1},  {1, 4, 4, 1},
-    {4, 4, 2, 1},  {2, 8, 1, 1},  {2, 8, 2, 1},  {2, 8, 3, 1},  {2, 8, 4, 1},
+    {4, 4, 2, 1},  {2, 8, 1, 1},  {2, 8, 2, 1},  {2, 8, 3, 1},  {2, 8, 4, 1},  {2, 8, 5, 1},
+    {2, 8, 6, 1},  {2, 8, 8, 1},
     {4, 4, 4, 1},  {4, 4, 8, 1},  {4, 4, 16, 1}, {8, 8, 4, 1},  {8, 8, 8, 1},
     {8, 8, 6, 2},  {8, 8, 12, 1}, {8, 8, 16, 1}, {8, 8, 24, 1}, {8, 8, 32, 1}, {8, 8, 4, 2},
     {8, 8, 4, 3},  {8, 8, 4, 4},  {8, 8, 8, 2},  {4, 4, 2, 2},  {4, 4, 4, 2},
@@ -427,32 +436,31 @@ static hipError_t launch_level(const MatchParamsDev& P, const FramesDev& FR, con
   OCSR_TILED(4, 4, 2, 2)
   OCSR_TILED(4, 4, 4, 2)
 #undef OCSR_TILED
-#define OCSR_HALF(C)                                                                        \
-  if (v.rows == 2 && v.cpl == C)                                                             \
-    return timed_launch(timer, name, match_level_kernel<dev::HalfMatcher<C>, 4>, dim3(grid), dim3(256), \
-                        0, stream, P, FR, ws, dbg, level);
-  OCSR_HALF(1)
-  OCSR_HALF(2)
-  OCSR_HALF(3)
-  OCSR_HALF(4)
-#undef OCSR_HALF
-  if (v.rows == 0)
-    return timed_launch(timer, name, match_level_kernel<dev::GenericMatcher, 4>, dim3(grid), dim3(256), 0,
-                        stream, P, FR, ws, dbg, level);
-  if (v.rows == 1 && v.cpl == 2)
-    return timed_launch(timer, name, match_level_kernel<dev::QuadMatcher<2>, 4>, dim3(grid), dim3(256), 0,
-                        stream, P, FR, ws, dbg, level);
-  if (v.rows == 1 && v.cpl == 4)
-    return timed_launch(timer, name, match_level_kernel<dev::QuadMatcher<4>, 4>, dim3(grid), dim3(256), 0,
-                        stream, P, FR, ws, dbg, level);
+  const bool want = dbg.blocks || dbg.cost_fwd || dbg.cost_bwd;
+#define OCSR_LEVEL(M, WAVES)                                                                  \
+  return timed_launch(timer, name, want ? match_level_kernel<M, WAVES, true> : match_level_kernel<M, WAVES, false>, \
+                      dim3(grid), dim3(256), 0, stream, P, FR, ws, dbg, level)
+#define OCSR_TWO(C)                                                                           \
+  if (v.rows == 2 && v.cpl == C) OCSR_LEVEL(dev::PairMatcher<C>, matrix_waves<C>())
+  OCSR_TWO(1);
+  OCSR_TWO(2);
+  OCSR_TWO(3);
+  OCSR_TWO(4);
+  OCSR_TWO(5);
+  OCSR_TWO(6);
+  OCSR_TWO(8);
+#undef OCSR_TWO
+  if (v.rows == 0) OCSR_LEVEL(dev::GenericMatcher, 4);
+  if (v.rows == 1 && v.cpl == 2) OCSR_LEVEL(dev::QuadMatcher<2>, 4);
+  if (v.rows == 1 && v.cpl == 4) OCSR_LEVEL(dev::QuadMatcher<4>, 4);
+#undef OCSR_LEVEL
   return hipErrorNotSupported;   // rejected by the argument checks before any launch
 }
 
 // One launch for both levels when a kernel for the pair of variants is built (with
 // launch == false: only whether it is built).
 #define COMMA ,
-static bool launch_pair(const MatchParamsDev& P, const FramesDev& FR, const MatchWs& ws,
-                        const DebugDev& dbg, int grid, hipStream_t stream, const LaunchTimer* timer,
+static bool launch_pair(const MatchParamsDev& P, const FramesDev& FR, const MatchWs& ws, int grid, hipStream_t stream, const LaunchTimer* timer,
                         bool launch) {
   const PathDev& f = P.path[0];
   const PathDev& c = P.path[1];
@@ -461,7 +469,7 @@ static bool launch_pair(const MatchParamsDev& P, const FramesDev& FR, const Matc
   if (f.rows == FRW && f.cpl == FCP && c.rows == CRW && c.cpl == CCP && c.passes == CPS) { \
     if (launch)                                                                          \
       timed_launch(timer, "match", match_pair_kernel<FRW, FXW, FCP, CRW, CXW, CCP, CPS>,    \
-                   dim3(grid), dim3(256), 0, stream, P, FR, ws, dbg);                     \
+                   dim3(grid), dim3(256), 0, stream, P, FR, ws);                          \
     return true;                                                                         \
   }
   OCSR_PAIR(4, 4, 2, 8, 8, 8, 1)
@@ -479,17 +487,21 @@ static bool launch_pair(const MatchParamsDev& P, const FramesDev& FR, const Matc
 #define OCSR_PAIR2(FM, FRW, FCP, FPS, CCP)                                                  \
   if (f.rows == FRW && f.cpl == FCP && f.passes == FPS && c.rows == 2 && c.cpl == CCP) {    \
     if (launch)                                                                          \
-      timed_launch(timer, "match", match_pair2_kernel<FM, dev::HalfMatcher<CCP>, 4>, dim3(grid),  \
-                   dim3(256), 0, stream, P, FR, ws, dbg);                                 \
+      timed_launch(timer, "match", match_pair2_kernel<FM, dev::PairMatcher<CCP>, matrix_waves<CCP>()>, dim3(grid),  \
+                   dim3(256), 0, stream, P, FR, ws);                                      \
     return true;                                                                         \
   }
   OCSR_PAIR2(dev::TiledMatcher<4 COMMA 4 COMMA 2 COMMA 1>, 4, 2, 1, 2)
   OCSR_PAIR2(dev::TiledMatcher<4 COMMA 4 COMMA 2 COMMA 1>, 4, 2, 1, 3)
   OCSR_PAIR2(dev::TiledMatcher<4 COMMA 4 COMMA 2 COMMA 1>, 4, 2, 1, 4)
-  OCSR_PAIR2(dev::HalfMatcher<1>, 2, 1, 1, 3)
-  OCSR_PAIR2(dev::HalfMatcher<2>, 2, 2, 1, 3)
-  OCSR_PAIR2(dev::HalfMatcher<2>, 2, 2, 1, 4)
-  OCSR_PAIR2(dev::HalfMatcher<3>, 2, 3, 1, 3)
+  OCSR_PAIR2(dev::PairMatcher<1>, 2, 1, 1, 3)
+  OCSR_PAIR2(dev::PairMatcher<2>, 2, 2, 1, 3)
+  OCSR_PAIR2(dev::PairMatcher<2>, 2, 2, 1, 4)
+  OCSR_PAIR2(dev::PairMatcher<3>, 2, 3, 1, 3)
+  OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 2)
+  OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 5)
+  OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 6)
+  OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 8)
   OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 3)
   OCSR_PAIR2(dev::QuadMatcher<2>, 1, 2, 1, 4)
   OCSR_PAIR2(dev::GenericMatcher, 0, 4, 1, 3)
@@ -581,13 +593,14 @@ hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr
     e = timed_launch(timer, "match", kernel, dim3(n_match_wgs), dim3(256), bytes, stream, P, FR, ws,
                      dbg, wb);
     if (e != hipSuccess) return e;
-  } else if ((level_launches == 2 || (level_launches == 0 && FR.n == 1)) &&
-             launch_pair(P, FR, ws, dbg, n_match_wgs, stream, nullptr, false)) {
+  } else if (!dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd &&
+             (level_launches == 2 || (level_launches == 0 && FR.n == 1)) &&
+             launch_pair(P, FR, ws, n_match_wgs, stream, nullptr, false)) {
     // one launch for both levels: in a one-frame call the far level alone cannot fill
     // the GPU, and its blocks fill the close level's tail (whole 1080p frame: 31 against
     // 38 us per frame); each level of a batch fills the GPU by itself, and there the two
     // forms are about even (16 frames: 117.5 against 10.3 + 109.2 us)
-    e = launch_pair(P, FR, ws, dbg, n_match_wgs, stream, timer, true) ? hipGetLastError() : hipErrorNotSupported;
+    e = launch_pair(P, FR, ws, n_match_wgs, stream, timer, true) ? hipGetLastError() : hipErrorNotSupported;
     if (e != hipSuccess) return e;
   } else {
     // close blocks first: they carry most of the work

@@ -70,8 +70,10 @@ struct MatchParamsDev {
   float fb;                        // focal_px * baseline_m, one fp32 multiply
   float d_eps;
   int32_t cap_blocks;              // block capacity of one frame
-  int32_t item_blocks[2];          // blocks per work item of each level: kItemWaves x
-                                   // the blocks one wave takes
+  int32_t group_x[2];              // horizontally adjacent blocks that one wave of a level's
+                                   // matcher takes together: 1, 2 or 4
+  int32_t item_blocks[2];          // such groups per work item of each level: kItemWaves x
+                                   // the groups one wave takes
   int32_t full_census;             // whole-frame calls: 1 = census of every tile, 0 = only
                                    // of the tiles some box's search reads
   int32_t vertical;                // 1: a vertical range is searched (the dy kernels run)
@@ -123,7 +125,7 @@ struct FramesDev {
   int32_t n_boxes_total;
 };
 
-// Per-box plan, written by the plan step (one 64-byte record per box).
+// Per-box plan, written by the plan step.
 struct BoxPlan {
   int32_t status;                  // -1: to be matched; else an OCSR_REASON_* code
   int32_t level;                   // 0 far, 1 close
@@ -136,13 +138,19 @@ struct BoxPlan {
   int32_t ioff;                    // first work item among the frame's boxes of its level
   int32_t frame;
 };
+static_assert(sizeof(BoxPlan) == 64, "one cache line per plan");
+
+// Groups of gx (1, 2 or 4) horizontally adjacent blocks in a grid of nbx x nby blocks.
+__host__ __device__ inline int32_t block_groups(int32_t nbx, int32_t nby, int32_t gx) {
+  return ((nbx + gx - 1) >> (gx >> 1)) * nby;
+}
 
 struct BoxClip {
   int32_t cx0, cy0, cx1, cy1;      // clipped box; empty boxes are all zero
 };
 
-// Matching work is dealt in items of up to item_blocks consecutive blocks of one box
-// (blocks per wave x the 4 waves of a 256-thread workgroup).
+// Matching work is dealt in items of up to item_blocks consecutive groups of blocks of one
+// box (groups per wave x the 4 waves of a 256-thread workgroup).
 constexpr int kItemWaves = 4;
 constexpr int kMaxBlocksPerWave = 8;
 
@@ -157,8 +165,8 @@ enum { GC_TIMEOUT = 0, GC_BAR0 = 8, GC_BAR1 = 16, GC_BAR2 = 24, GC_N = 32 };
 // A work item: the box, the item's first block and the box's block geometry.
 struct ItemRec {
   int32_t k;                       // box within the frame
-  int32_t first;                   // the item's first block (0-based within the box)
-  int32_t nblk, off;               // the box's blocks and its first block number
+  int32_t first;                   // the item's first group (0-based within the box)
+  int32_t nblk, ngrp, off;         // the box's blocks, groups and first block number
   int32_t nbx, bw, bh, ox, oy;     // block grid
   int32_t lx0, ly0, lw, lh;        // level box
 };

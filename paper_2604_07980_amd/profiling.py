@@ -32,10 +32,13 @@ KERNEL_SOURCES = {
                "paper_2604_07980_amd/csrc/dev_match.hpp", "paper_2604_07980_amd/csrc/dev_common.hpp",
                "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
+              "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
               "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match_close": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
+              "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
                     "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match_far": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
+              "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
                   "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "plan": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
              "paper_2604_07980_amd/csrc/dev_census.hpp", "paper_2604_07980_amd/csrc/dev_common.hpp",
@@ -43,7 +46,8 @@ KERNEL_SOURCES = {
     "aggregate": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
                   "paper_2604_07980_amd/csrc/dev_common.hpp",
                   "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
-    "dense": ["paper_2604_07980_amd/csrc/dense.hip", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
+    "dense": ["paper_2604_07980_amd/csrc/dense.hip", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
+              "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
 }
 
 # rocprofv3 kernel names (demangled) of each reported kernel
@@ -51,10 +55,11 @@ KERNEL_PATTERNS = {
     "census": r"frame_census_kernel|census_list_kernel",
     "plan": r"plan_tiles_kernel",
     "match": r"match_pair_kernel|match_tiled_kernel|match_pair2_kernel|match_level_kernel",
-    # the batch workload's tuned variants: the row-half matcher serves the close level,
-    # the generic or four-block matcher the far level
-    "match_close": r"match_level_kernel<ocsr::dev::HalfMatcher",
-    "match_far": r"match_level_kernel<ocsr::dev::(GenericMatcher|QuadMatcher)",
+    # the batch workload's variants: two 8 x 8 blocks per wave at the close level, four
+    # 4 x 4 blocks or the generic matcher at the far level (HalfMatcher and QuadMatcher: the
+    # names in earlier traces)
+    "match_close": r"match_level_kernel<ocsr::dev::(HalfMatcher|MatrixMatcher<2,)",
+    "match_far": r"match_level_kernel<ocsr::dev::(GenericMatcher|QuadMatcher|MatrixMatcher<4,)",
     "aggregate": r"aggregate_kernel",
     "dense": r"dense_kernel",
     "copy": r"copyBuffer",
