@@ -310,6 +310,12 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
     if (lds > kDyMaxWgLds)
       return fail(OCSR_E_UNSUPPORTED, "%s path: %d disparities x %d vertical offsets need %zu bytes of "
                   "LDS per workgroup > %zu", l == 0 ? "far" : "close", ph.nd, ph.ndy, lds, kDyMaxWgLds);
+    // the matrix-core matchers serve every vertical range, whatever variant was chosen: four
+    // 4 x 4 blocks per wave up to 64 candidates, else two blocks per wave
+    ph.rows = rows == 4 && ph.nd <= 64 ? 1 : 2;
+    ph.cpl = ph.rows == 1 ? (ph.nd <= 32 ? 2 : 4) : (ph.nd + 31) / 32;
+    if (ph.cpl == 7) ph.cpl = 8;
+    ph.passes = 1;
   }
   if (p->lr_tol < 0) return fail(OCSR_E_INVALID, "lr_tol < 0");
   if (p->min_point_pct < 0 || p->min_point_pct > 100) return fail(OCSR_E_INVALID, "min_point_pct outside 0..100");
@@ -332,9 +338,9 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
   d->d_eps = p->d_eps;
   d->cap_blocks = cap_blocks;
   // a wave of the matrix-core kernels takes four (rows = 1) or two (rows = 2) adjacent blocks
-  // together; the vertical kernels and all others one
+  // together, of the others one
   for (int l = 0; l < 2; ++l) {
-    d->group_x[l] = d->vertical ? 1 : d->path[l].rows == 1 ? 4 : d->path[l].rows == 2 ? 2 : 1;
+    d->group_x[l] = d->path[l].rows == 1 ? 4 : d->path[l].rows == 2 ? 2 : 1;
     d->item_blocks[l] = kItemWaves * (d->group_x[l] == 4 ? 1 : ctx->blocks_per_wave);
   }
   d->full_census = ctx->full_census;

@@ -671,208 +671,6 @@ __device__ __forceinline__ void match_block_generic(const MatchParamsDev& P, con
   wave_sync();
 }
 
-// ---------------------------------------------------------------------------------
-// TILED block with a vertical range (the census cost over (dx, dy), Sec. 4.3.2). The
-// register-blocked row costs of match_block_tiled, repeated for every vertical offset.
-// Consecutive offsets read strip rows moved by one. When all ROWS + ndy - 1 rows fit
-// kDyFullLoads loads per lane (short strips) they are staged at once; otherwise the
-// strip lives in an LDS ring of ROWS + 1 rows: step t reads rows t .. t + ROWS - 1 (lane row j from ring slot
-// (t + j) mod (ROWS + 1)) while row t + ROWS, which step t + 1 needs, is loaded into the
-// one slot step t does not read. Each row is loaded once per direction, its latency
-// hidden behind the previous step. Rows and columns outside the level image read as
-// zero. Every (d, e) cost is kept in LDS (uint16) for the parabola, which runs along d at
-// the winning e; keys order ties by d, then e.
-// LDS per wave: dy_wave_lds_bytes(ROWS, nd, ndy).
-// ---------------------------------------------------------------------------------
-// the CH chunks of strip row y (words x_first + 64 c + lane, zero outside the image or
-// at and past sw)
-template <int CH>
-__device__ __forceinline__ void load_row_dy(uint64_t (&w)[CH], const uint64_t* __restrict__ img,
-                                            int pitch, int W, int H, int x_first, int y, int sw,
-                                            int lane) {
-  const bool row_ok = y >= 0 && y < H;
-#pragma unroll
-  for (int c = 0; c < CH; ++c) {
-    const int m = 64 * c + lane, x = x_first + m;
-    const bool ok = row_ok && m < sw && x >= 0 && x < W;
-    w[c] = img[ok ? (size_t)y * pitch + x : 0];
-    w[c] = ok ? w[c] : 0ull;
-  }
-}
-
-template <int CH>
-__device__ __forceinline__ void store_row_dy(uint64_t* __restrict__ slot, const uint64_t (&w)[CH],
-                                             int SWr, int lane) {
-#pragma unroll
-  for (int c = 0; c < CH; ++c)
-    if (64 * c + lane < SWr) slot[64 * c + lane] = w[c];
-}
-
-// One direction's search over every (d, e): rows y_top + t + jj for steps t = 0 .. ndy-1,
-// strip columns from x_first. Step t is vertical index e = (fwd ? t : ndy - 1 - t); strip
-// position q is candidate index (fwd ? nd - 1 - q : q). Returns the lane's least key
-// (cost << 16 | (d index * ndy + e)); costs go to cost[d index * ndy + e].
-template <int ROWS, int NX, int CPL, int CH>
-__device__ __forceinline__ uint32_t search_dy(const uint64_t (&t)[NX], uint64_t* __restrict__ S,
-                                              int SWr, int passes, const uint64_t* __restrict__ img,
-                                              int pitch, int W, int H, int x_first, int y_top,
-                                              int ny, int sw, int nd, int ndy, bool fwd,
-                                              uint32_t rowmask, uint32_t col_all, uint32_t col_any,
-                                              uint16_t* __restrict__ cost, int lane) {
-  constexpr int NR = ROWS + 1;
-  constexpr int PC = (64 / ROWS) * CPL;
-  static_assert(PC == kDyPass, "a pass covers kDyPass candidates");
-  const int j = lane % ROWS, grp = lane / ROWS;
-  // all ROWS + ndy - 1 rows at once when they fit (wave-uniform), else the ring
-  const bool full = dy_full(ROWS, nd, ndy);
-  if (full) {
-    // word idx = lane + 64 k of the rows x SWr block, every load issued before a store
-    const int n = (ROWS + ndy - 1) * SWr;
-    uint64_t w[kDyFullLoads];
-#pragma unroll
-    for (int k = 0; k < kDyFullLoads; ++k) {
-      const int idx = lane + 64 * k;
-      const int r = idx / SWr, m = idx - r * SWr, x = x_first + m, y = y_top + r;
-      const bool ok = idx < n && m < sw && x >= 0 && x < W && y >= 0 && y < H;
-      w[k] = img[ok ? (size_t)y * pitch + x : 0];
-      w[k] = ok ? w[k] : 0ull;
-    }
-#pragma unroll
-    for (int k = 0; k < kDyFullLoads; ++k)
-      if (lane + 64 * k < n) S[lane + 64 * k] = w[k];
-  } else {
-    // rows 0 .. ROWS - 1, every load issued before the first store
-    uint64_t w[ROWS][CH];
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) load_row_dy<CH>(w[r], img, pitch, W, H, x_first, y_top + r, sw, lane);
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) store_row_dy<CH>(S + r * SWr, w[r], SWr, lane);
-  }
-  wave_sync();
-  uint32_t key = 0xFFFFFFFFu;
-  uint32_t acc[CPL];
-  for (int st = 0; st < ndy; ++st) {
-    const bool more = !full && st + 1 < ndy;
-    uint64_t pre[CH];
-    if (more) load_row_dy<CH>(pre, img, pitch, W, H, x_first, y_top + st + ROWS, sw, lane);
-    const int e = fwd ? st : ndy - 1 - st;
-    const uint64_t* srow = S + (full ? st + j : (st + j) % NR) * SWr;
-    for (int ps = 0; ps < passes; ++ps) {
-      if (j < ny) row_costs<NX, CPL>(t, srow + ps * PC + grp * CPL, rowmask, col_all, col_any, acc);
-#pragma unroll
-      for (int cc = 0; cc < CPL; ++cc)
-        if (j >= ny) acc[cc] = 0;
-#pragma unroll
-      for (int cc = 0; cc < CPL; ++cc) {
-        const uint32_t tot = row_sum<ROWS>(acc[cc]);
-        const int q = ps * PC + grp * CPL + cc;
-        if (q < nd) {
-          const int id = (fwd ? nd - 1 - q : q) * ndy + e;
-          key = min(key, (tot << 16) | (uint32_t)id);
-          if (j == 0) cost[id] = (uint16_t)tot;
-        }
-      }
-    }
-    // the slot of row st - 1, which step st does not read
-    if (more) {
-      store_row_dy<CH>(S + ((st + ROWS) % NR) * SWr, pre, SWr, lane);
-      wave_sync();
-    }
-  }
-  wave_sync();   // every read of S and write of cost done before the caller goes on
-  return key;
-}
-
-template <int ROWS, int NX>
-__device__ __forceinline__ void match_block_dy(const MatchParamsDev& P, const FrameDev& fr,
-                                               const MatchWs& ws, const DebugDev& dbg,
-                                               const BlockCtx& c, int lane, void* lds) {
-  constexpr int CPL = dy_cpl(ROWS);
-  constexpr int CH = dy_chunks(ROWS);
-  const LevelDev& lv = fr.lv[c.level];
-  const PathDev& ph = P.path[c.level];
-  const int nd = ph.nd, dlo = ph.dlo, dhi = dlo + nd - 1;
-  const int ndy = ph.ndy, dylo = ph.dylo;
-  const int passes = (nd + kDyPass - 1) / kDyPass;
-  const int SWr = passes * kDyPass + NX - 1;   // strip row stride (words)
-  const int sw = nd + NX - 1;                  // words a row's candidates read
-  auto r16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
-  uint64_t* S = (uint64_t*)lds;
-  uint64_t* T = (uint64_t*)((char*)lds + r16(sizeof(uint64_t) * dy_lds_rows(ROWS, nd, ndy) * SWr));
-  uint16_t* costf = (uint16_t*)((char*)T + r16(sizeof(uint64_t) * ROWS * NX));
-  uint16_t* costb = (uint16_t*)((char*)costf + r16(sizeof(uint16_t) * (size_t)nd * ndy));
-  const int j = lane % ROWS;
-  const int nx = c.g.nx, ny = c.g.ny;
-  const int X0 = c.g.cx, Y0 = c.g.cy;
-
-  // forward template CL(X0 + i, Y0 + j): the block lies inside the level image
-  for (int idx = lane; idx < ROWS * NX; idx += 64) {
-    const int jj = idx / NX, i = idx % NX;
-    T[idx] = jj < ny && i < nx ? lv.L[(size_t)(Y0 + jj) * lv.pitch + X0 + i] : 0ull;
-  }
-  const uint64_t mask = block_mask(ws, fr.box_off, fr.n_boxes, c.k, c.g, lane);
-  const bool eligible = block_eligible(P, mask, nx * ny);
-  wave_sync();
-  if (!eligible) {
-    write_block(ws, dbg, c, ph, mask, false, dlo, dlo, 0, (float)dlo, 0, lane);
-    wave_sync();
-    return;
-  }
-  const uint32_t rowmask = j < ny ? (uint32_t)((mask >> (j * nx)) & ((1u << nx) - 1u)) : 0u;
-  uint32_t col_all = (1u << nx) - 1u, col_any = 0;
-  for (int jj = 0; jj < ny; ++jj) {
-    const uint32_t r = (uint32_t)((mask >> (jj * nx)) & ((1u << nx) - 1u));
-    col_all &= r;
-    col_any |= r;
-  }
-  uint64_t t[NX];
-#pragma unroll
-  for (int i = 0; i < NX; ++i) t[i] = T[j * NX + i];
-  // forward: strip row of step e holds CR(X0 - dhi + m, Y0 + dylo + e + jj); entry q + i
-  // holds CR(X0 + i - d) for d = dhi - q
-  uint32_t key = search_dy<ROWS, NX, CPL, CH>(t, S, SWr, passes, lv.R, lv.pitch, lv.W, lv.H,
-                                               X0 - dhi, Y0 + dylo, ny, sw, nd, ndy, true,
-                                               rowmask, col_all, col_any, costf, lane);
-  key = wave_min_u32(key, ROWS);
-  const int best_id = (int)(key & 0xFFFFu);
-  const int kf = best_id / ndy, ef = best_id - kf * ndy;
-  const int d_f = dlo + kf, dy_f = dylo + ef;
-  const int ca = (int)costf[max(kf - 1, 0) * ndy + ef];
-  const int cb = (int)costf[min(kf + 1, nd - 1) * ndy + ef];
-  const float d_sub = subpixel(d_f, kf, nd, ca, (int)(key >> 16), cb);
-  // backward template CR(X0 - d_f + i, Y0 + dy_f + j), zero outside the image
-  {
-    const int y = Y0 + dy_f + j;
-    const bool row_ok = j < ny && y >= 0 && y < lv.H;
-#pragma unroll
-    for (int i = 0; i < NX; ++i) {
-      const int x = X0 - d_f + i;
-      const bool ok = row_ok && i < nx && x >= 0 && x < lv.W;
-      t[i] = lv.R[ok ? (size_t)y * lv.pitch + x : 0];
-      t[i] = ok ? t[i] : 0ull;
-    }
-  }
-  // backward: offset e reads CL(X0 - d_f + dlo + m, Y0 + dy_f - dylo - e + jj); the steps
-  // run e from the last offset down, so that the rows move down by one per step
-  uint32_t bkey = search_dy<ROWS, NX, CPL, CH>(t, S, SWr, passes, lv.L, lv.pitch, lv.W, lv.H,
-                                                X0 - d_f + dlo, Y0 + dy_f - dylo - (ndy - 1), ny,
-                                                sw, nd, ndy, false, rowmask, col_all, col_any,
-                                                costb, lane);
-  bkey = wave_min_u32(bkey, ROWS);
-  const int bid = (int)(bkey & 0xFFFFu);
-  const int kb = bid / ndy, eb = bid - kb * ndy;
-  const int d_b = dlo + kb, dy_b = dylo + eb;
-  const int lr_ok = abs(d_b - d_f) <= P.lr_tol;   // consistency on d only (Sec. 4.3.3)
-  if (c.b < dbg.cap_blocks && (dbg.cost_fwd || dbg.cost_bwd)) {
-    for (int q = lane; q < nd && q < dbg.cap_nd; q += 64) {
-      if (dbg.cost_fwd) dbg.cost_fwd[(size_t)c.b * dbg.cap_nd + q] = costf[q * ndy + ef];
-      if (dbg.cost_bwd) dbg.cost_bwd[(size_t)c.b * dbg.cap_nd + q] = costb[q * ndy + eb];
-    }
-  }
-  write_block(ws, dbg, c, ph, mask, true, d_f, d_b, lr_ok, d_sub, lr_ok, lane, dy_f, dy_b);
-  wave_sync();
-}
-
 // Work item of frame f at `level`: wave w of the workgroup runs blocks
 // r.first + w + 4 j of the box that exist.
 __device__ __forceinline__ BoxPlan item_plan(const ItemRec& r, int f, int level) {

@@ -16,6 +16,11 @@
 // ranges start within 16 - BS columns of each other (32 - BS with one more tile) share a
 // pass, which neighbouring blocks of one surface do; the others take a pass of their own.
 //
+// With a vertical range (the census cost over (dx, dy), Sec. 4.3.2) each direction repeats
+// the strip for every vertical offset, its rows moved by one, and keeps the costs of the
+// offset that has the least so far; blocks share a backward pass when their forward
+// offsets are equal too.
+//
 // Bound: vector ALU. Two 8 x 8 blocks and 96 candidates take about 280 instructions and 28
 // products a direction, against 1120 for XORs and popcounts of every term.
 #pragma once
@@ -101,17 +106,20 @@ __device__ __forceinline__ bool scan_hidden(const MatchWs& ws, int box_off, int 
 }
 
 // Column sums of the group against 16 T (wide: 16 TB) strip columns from x_first on, into
-// V[column * VS + group column / 2] as packed 16-bit sums. rows: the block's first row of the
-// strip's view; a: the group's digits. Columns outside the image read as 0. Rows past the
-// block's ny (whose points do not count) read row ny - 1.
-template <class M>
-__device__ __forceinline__ void strip_sums(const uint64_t* __restrict__ rows, int pitch, int x_first,
-                                           int ny, int W, bool wide, const v4i (&a)[M::G][2],
+// V[column * VS + group column / 2] as packed 16-bit sums. The strip's rows are y_first .. of
+// img; a: the group's digits. Columns outside the image read as 0, and with VERT rows too
+// (else every row is inside). Rows past the block's ny (whose points do not count) read row
+// ny - 1.
+template <class M, bool VERT>
+__device__ __forceinline__ void strip_sums(const uint64_t* __restrict__ img, const LevelDev& lv, int x_first,
+                                           int y_first, int ny, bool wide, const v4i (&a)[M::G][2],
                                            uint32_t* __restrict__ V, int lane) {
+  const int W = lv.W, pitch = lv.pitch;
   constexpr int T = M::T, TB = M::TB, G = M::G;
   const int n = lane & 15, kq = lane >> 4;
   uint64_t w[G][TB];
-  if (x_first >= 0 && x_first + 16 * TB <= W) {
+  if (x_first >= 0 && x_first + 16 * TB <= W && (!VERT || (y_first >= 0 && y_first + ny <= lv.H))) {
+    const uint64_t* __restrict__ rows = uniform(img + (size_t)y_first * pitch);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const uint64_t* p = rows + (size_t)min(kq + 4 * g, ny - 1) * pitch + (x_first + n);
@@ -122,11 +130,13 @@ __device__ __forceinline__ void strip_sums(const uint64_t* __restrict__ rows, in
   } else {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const uint64_t* p = rows + (size_t)min(kq + 4 * g, ny - 1) * pitch;
+      const int y = y_first + min(kq + 4 * g, ny - 1);
+      const bool y_in = !VERT || (y >= 0 && y < lv.H);
+      const uint64_t* p = img + (size_t)(y_in ? y : 0) * pitch;
 #pragma unroll
       for (int t = 0; t < TB; ++t) {
         const int x = x_first + 16 * t + n;
-        const bool ok = x >= 0 && x < W;
+        const bool ok = y_in && x >= 0 && x < W;
         w[g][t] = p[ok ? x : 0];
         w[g][t] = ok ? w[g][t] : 0ull;
       }
@@ -197,8 +207,9 @@ __device__ __forceinline__ uint32_t block_min(uint32_t v, int lane) {
   return v;
 }
 
-// Blocks u .. u + NB - 1 (those below nbx) of block row v of a box.
-template <int NB, int CPL>
+// Blocks u .. u + NB - 1 (those below nbx) of block row v of a box. VERT: over the path's
+// vertical offsets, else at none.
+template <int NB, int CPL, bool VERT>
 __device__ __forceinline__ void match_group(const MatchParamsDev& P, const FrameDev& fr, const MatchWs& ws,
                                             const DebugDev& dbg, int f, int level, const ItemRec& r,
                                             int u, int v, const OccLanes& oc, int lane, void* lds) {
@@ -209,12 +220,10 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
   const LevelDev& lv = fr.lv[level];
   const PathDev& ph = P.path[level];
   const int nd = ph.nd, dlo = ph.dlo, dhi = dlo + nd - 1;
-  const int nx = r.bw, ny = r.bh, W = lv.W, s = lv.scale;
+  const int ndy = VERT ? ph.ndy : 1, dylo = VERT ? ph.dylo : 0;
+  const int nx = r.bw, ny = r.bh, s = lv.scale;
   const int nb = min(NB, r.nbx - u);
   const int X0 = r.ox + u * nx, Y0 = r.oy + v * ny;
-  const uint64_t* __restrict__ Lb = uniform(lv.L + (size_t)Y0 * lv.pitch);
-  const uint64_t* __restrict__ Rb = uniform(lv.R + (size_t)Y0 * lv.pitch);
-
   // points kept (Sec. 4.3.5): bit j BS + i of block b's mask, 64 points per ballot
   constexpr int NM = NB * BS * BS / 64;         // ballots: 2 (a block each) or 1 (four blocks)
   uint64_t mask[NM];
@@ -266,7 +275,7 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
     keep[g] = (bits & 1u) ? 0xFFFFFFFFu : 0u;
   }
   float d_sub = (float)dlo;
-  int d_f = dlo, d_b = dlo, lr_ok = 0;
+  int d_f = dlo, d_b = dlo, dy_f = 0, dy_b = 0, lr_ok = 0;
   if (eligible) {
     // the group's digits from its words t (rows kq + 4 g)
     v4i a[G][2];
@@ -291,107 +300,138 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
       return __shfl(q, b * BS, 64) - BS * (int)M::kBias;
     };
     const int bg = r.off + v * r.nbx + u + b;   // block number within the frame
+    // debug output: the costs kept in LDS as true ones, add: what they lack
+    auto put_costs = [&](uint16_t* out, int add) {
+      wave_sync();
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        const int kc = e0 + c;
+        if (mine && kc < nd && kc < dbg.cap_nd && bg < dbg.cap_blocks)
+          out[(size_t)bg * dbg.cap_nd + kc] = (uint16_t)(((int)costf[b * NC + kc] + add) >> 1);
+      }
+    };
     uint64_t t[G];
     {
+      const uint64_t* __restrict__ Lb = uniform(lv.L + (size_t)Y0 * lv.pitch);
       const int x = X0 + tb * nx + ti;
 #pragma unroll
       for (int g = 0; g < G; ++g) t[g] = Lb[keep[g] ? (size_t)(kq + 4 * g) * lv.pitch + x : 0];
     }
     digits(t);
-    // forward: strip position q of block 0 is column X0 - dhi + q, candidate e is d = dhi - e
-    strip_sums<M>(Rb, lv.pitch, X0 - dhi, ny, W, false, a, V, lane);
-    wave_sync();
+    // forward: strip position q of block 0 is column X0 - dhi + q, candidate e is d = dhi - e.
+    // A key is the cost (twice the Hamming sum plus a constant of the block) << 16 | (d - dlo)
+    // ndy + (dy - dylo)
     uint32_t cost[CPL];
-    diagonal_costs<M>(V, b, b * nx + e0, cost);
     uint32_t key = 0xFFFFFFFFu;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      const int e = e0 + c, kc = nd - 1 - e;
-      const bool in = e < nd;
-      key = min(key, in ? (cost[c] & 0xFFFF0000u) | (uint32_t)kc : 0xFFFFFFFFu);
-      costf[b * NC + (in ? kc : e)] = cost[c] >> 16;
-    }
-    key = block_min<LB>(key, lane);
-    if (want_costs && dbg.cost_fwd) {
-      const int add = rest(t);
+    for (int ey = 0; ey < ndy; ++ey) {
+      strip_sums<M, VERT>(lv.R, lv, X0 - dhi, Y0 + dylo + ey, ny, false, a, V, lane);
+      wave_sync();
+      diagonal_costs<M>(V, b, b * nx + e0, cost);
+      uint32_t k = 0xFFFFFFFFu;
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
-        const int kc = nd - 1 - (e0 + c);
-        if (mine && kc >= 0 && kc < dbg.cap_nd && bg < dbg.cap_blocks)
-          dbg.cost_fwd[(size_t)bg * dbg.cap_nd + kc] = (uint16_t)(((int)(cost[c] >> 16) + add) >> 1);
+        const int e = e0 + c, kc = nd - 1 - e;
+        k = min(k, e < nd ? (cost[c] & 0xFFFF0000u) | (uint32_t)(VERT ? kc * ndy + ey : kc) : 0xFFFFFFFFu);
       }
+      k = block_min<LB>(k, lane);
+      if (!VERT || k < key) {
+        key = k;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          const int e = e0 + c, kc = nd - 1 - e;
+          costf[b * NC + (e < nd ? kc : e)] = cost[c] >> 16;
+        }
+      }
+      if (VERT) wave_sync();
     }
-    const int best = (int)(key & 0xFFFFu);
+    if (want_costs && dbg.cost_fwd) put_costs(dbg.cost_fwd, rest(t));
+    const int id = (int)(key & 0xFFFFu);
+    const int best = VERT ? id / ndy : id;
     d_f = dlo + best;
+    if (VERT) dy_f = dylo + id - best * ndy;
     wave_sync();
-    // the costs here are twice the Hamming sums plus a constant of the block: the parabola's
-    // numerator and denominator are both twice theirs, and their quotient the same number
+    // the parabola's numerator and denominator are both twice those of the Hamming sums, and
+    // their quotient the same number
     const int ca = (int)costf[b * NC + max(best - 1, 0)];
     const int cb = (int)costf[b * NC + min(best + 1, nd - 1)];
     if (mine) d_sub = subpixel(d_f, best, nd, ca, (int)(key >> 16), cb);
 
-    // backward: the group's columns are CR(x - d_f), candidate e of block b is strip column
-    // start[b] + e
-    int start[NB], df[NB];
+    // backward: the group's columns are CR(x - d_f) in rows y + dy_f, candidate e of block b is
+    // strip column start[b] + e, in rows y + dy_f - dy
+    int start[NB], df[NB], ef[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       df[q] = __builtin_amdgcn_readlane(d_f, q * LB);
+      ef[q] = VERT ? __builtin_amdgcn_readlane(dy_f, q * LB) : 0;
       start[q] = X0 + q * nx - df[q] + dlo;
     }
     {
-      int dt = df[0];
+      int dt = df[0], et = ef[0];
 #pragma unroll
-      for (int q = 1; q < NB; ++q) dt = tb == q ? df[q] : dt;
+      for (int q = 1; q < NB; ++q) {
+        dt = tb == q ? df[q] : dt;
+        et = tb == q ? ef[q] : et;
+      }
+      const uint64_t* __restrict__ Rb = uniform(VERT ? lv.R : lv.R + (size_t)Y0 * lv.pitch);
       const int x = X0 + tb * nx + ti - dt;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const bool ok = keep[g] && x >= 0;
-        t[g] = Rb[ok ? (size_t)(kq + 4 * g) * lv.pitch + x : 0];
+        const int y = (VERT ? Y0 + et : 0) + kq + 4 * g;
+        const bool ok = keep[g] && x >= 0 && (!VERT || (y >= 0 && y < lv.H));
+        t[g] = Rb[ok ? (size_t)y * lv.pitch + x : 0];
         t[g] = ok ? t[g] : 0ull;
       }
     }
     digits(t);
-    const int add_b = want_costs ? rest(t) : 0;
     uint32_t left = eligible, bkey = 0xFFFFFFFFu;
+    if (want_costs) wave_sync();                // the forward costs are read
     while (left) {
-      int base = 0x7FFFFFFF, far = 0;
+      int base = 0x7FFFFFFF, bdy = 0, far = 0;
 #pragma unroll
       for (int q = 0; q < NB; ++q)
-        if ((left >> q) & 1u) base = min(base, start[q]);
+        if (((left >> q) & 1u) && start[q] < base) {
+          base = start[q];
+          bdy = ef[q];
+        }
       uint32_t now = 0;
       int off = 0;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         const int o = start[q] - base;
-        if (((left >> q) & 1u) && o <= 32 - BS) {
+        if (((left >> q) & 1u) && o <= 32 - BS && (!VERT || ef[q] == bdy)) {
           now |= 1u << q;
           far = max(far, o);
           off = b == q ? o : off;
         }
       }
       left &= ~now;
-      strip_sums<M>(Lb, lv.pitch, base, ny, W, far > 16 - BS, a, V, lane);
-      wave_sync();
-      diagonal_costs<M>(V, b, off + e0, cost);
       const bool here = (now >> b) & 1u;
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const int e = e0 + c;
-        if (here && e < nd) bkey = min(bkey, (cost[c] & 0xFFFF0000u) | (uint32_t)e);
-      }
-      if (want_costs && dbg.cost_bwd) {
+      for (int ey = 0; ey < ndy; ++ey) {
+        strip_sums<M, VERT>(lv.L, lv, base, VERT ? Y0 + bdy - dylo - ey : Y0, ny, far > 16 - BS, a, V, lane);
+        wave_sync();
+        diagonal_costs<M>(V, b, off + e0, cost);
+        uint32_t k = 0xFFFFFFFFu;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
           const int e = e0 + c;
-          if (here && e < nd && e < dbg.cap_nd && bg < dbg.cap_blocks)
-            dbg.cost_bwd[(size_t)bg * dbg.cap_nd + e] = (uint16_t)(((int)(cost[c] >> 16) + add_b) >> 1);
+          k = min(k, here && e < nd ? (cost[c] & 0xFFFF0000u) | (uint32_t)(VERT ? e * ndy + ey : e) : 0xFFFFFFFFu);
         }
+        if (VERT || want_costs) k = block_min<LB>(k, lane);
+        if (want_costs && k < bkey) {
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) costf[b * NC + e0 + c] = cost[c] >> 16;
+        }
+        bkey = min(bkey, k);
+        wave_sync();
       }
-      wave_sync();
     }
-    bkey = block_min<LB>(bkey, lane);
-    d_b = dlo + (int)(bkey & 0xFFFFu);
-    lr_ok = mine && abs(d_b - d_f) <= P.lr_tol;
+    if (!VERT) bkey = block_min<LB>(bkey, lane);
+    if (want_costs && dbg.cost_bwd) put_costs(dbg.cost_bwd, rest(t));
+    const int bid = (int)(bkey & 0xFFFFu);
+    const int bb = VERT ? bid / ndy : bid;
+    d_b = dlo + bb;
+    if (VERT) dy_b = dylo + bid - bb * ndy;
+    lr_ok = mine && abs(d_b - d_f) <= P.lr_tol;   // consistency on d only (Sec. 4.3.3)
   }
   if (writer) {
     ws.blk_val[slot] = (float)s * d_sub;        // d_full = s * d (Sec. 4.1)
@@ -413,7 +453,7 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
       rec.d_f = mine ? d_f : dlo; rec.d_b = mine ? d_b : dlo;
       rec.lr_ok = lr_ok; rec.d_sub = d_sub; rec.valid = lr_ok;
       rec.dlo = dlo; rec.nd = nd;
-      rec.dy_f = 0; rec.dy_b = 0;
+      rec.dy_f = mine ? dy_f : 0; rec.dy_b = mine ? dy_b : 0;
       dbg.blocks[bg] = rec;
     }
   }
@@ -421,7 +461,7 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
 
 // Matcher of one level's TILED blocks: wave w of a workgroup takes groups r.first + w,
 // r.first + w + 4, ... of an item.
-template <int NB, int CPL>
+template <int NB, int CPL, bool VERT = false>
 struct MatrixMatcher {
   static constexpr size_t kLds = (Matrix<NB, CPL>::kLdsBytes + 15) & ~(size_t)15;
   using State = OccLanes;
@@ -437,7 +477,7 @@ struct MatrixMatcher {
     int g = r.first + wave;
     int v = g / ngx, ug = g - v * ngx;
     for (int j = wave; j < P.item_blocks[level]; j += kItemWaves) {
-      if (g < r.ngrp) match_group<NB, CPL>(P, fr, ws, dbg, f, level, r, NB * ug, v, oc, lane, lds);
+      if (g < r.ngrp) match_group<NB, CPL, VERT>(P, fr, ws, dbg, f, level, r, NB * ug, v, oc, lane, lds);
       g += kItemWaves;
       ug += kItemWaves;
       while (ug >= ngx) {

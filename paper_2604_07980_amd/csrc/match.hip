@@ -6,8 +6,7 @@
 // boundaries. The device steps are in dev_census.hpp and dev_match.hpp, shared with
 // the fused persistent kernel.
 #include "dev_census.hpp"
-#include "dev_match.hpp"
-#include "dev_matrix.hpp"
+#include "match_kernels.hpp"
 
 namespace ocsr {
 namespace {
@@ -197,129 +196,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves<
     } else {
       dev::run_item_rec(P, fr, f, 0, r, wave, [&](const dev::BlockCtx& c) {
         dev::match_block_tiled<FR_, FX, FC>(P, fr, ws, dbg, c, lane, wl);
-      });
-    }
-  }
-}
-
-// Both levels in one launch with any pair of matchers (FM far, CM close): work items of
-// every frame's close level first, then of every far level. Compiled for WAVES waves per
-// SIMD. (Calls with debug output take one launch per level.)
-template <class FM, class CM, int WAVES>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void match_pair2_kernel(
-    MatchParamsDev P, FramesDev FR, MatchWs ws) {
-  const DebugDev dbg = {};
-  constexpr size_t kWave = FM::kLds > CM::kLds ? FM::kLds : CM::kLds;
-  __shared__ uint64_t lds[(kItemWaves * kWave + 7) / 8];
-  __shared__ int prefix[2 * kMaxFrames + 1];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  const int F = FR.n;
-  if (threadIdx.x < 64) {
-    const int j = lane < F ? lane : lane - F;
-    const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt);
-    if (lane < 2 * F) prefix[lane + 1] = incl;
-    if (lane == 0) prefix[0] = 0;
-  }
-  __syncthreads();
-  void* wl = (char*)lds + wave * kWave;
-  // the close items of every frame, then the far ones, dealt XCD by XCD as two lists
-  const int n_close = prefix[F];
-  const dev::Deal2 dl = dev::xcd_deal2(n_close, prefix[2 * F] - n_close);
-  for (int i = dl.first; i < dl.end; i += dl.step) {
-    const int m = dl.at(i);
-    int slot = 0;
-    for (int k = 1; k < 2 * F; ++k)
-      if (m >= prefix[k]) slot = k;
-    const int f = slot < F ? slot : slot - F;
-    const FrameDev& fr = FR.f[f];
-    const int q = m - prefix[slot];
-    // the lane index passes through an empty asm statement per item, so that neither
-    // matcher's per-lane indexing is held in registers across the loop (both would be)
-    int il = lane;
-    asm volatile("" : "+v"(il));
-    if (slot < F) {
-      const typename CM::State st = CM::frame_state(ws, fr, il);
-      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 1, q, il);
-      CM::run_item(P, fr, ws, dbg, f, 1, r, wave, il, wl, st);
-    } else {
-      const typename FM::State st = FM::frame_state(ws, fr, il);
-      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 0, q, il);
-      FM::run_item(P, fr, ws, dbg, f, 0, r, wave, il, wl, st);
-    }
-  }
-}
-
-// Waves per SIMD the matrix-core matchers are compiled for (their strip and accumulators
-// grow with the candidates per lane; checked in the built code: no spills).
-template <int CPL>
-constexpr int matrix_waves() { return CPL <= 4 ? 4 : CPL <= 6 ? 3 : 2; }
-
-// One level with any matcher. Without DBG no debug output is asked for, and its code and
-// pointers are not in the kernel.
-template <class M, int WAVES, bool DBG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void match_level_kernel(
-    MatchParamsDev P, FramesDev FR, MatchWs ws, DebugDev dbg_, int level) {
-  const DebugDev dbg = DBG ? dbg_ : DebugDev{};
-  __shared__ uint64_t lds[(kItemWaves * M::kLds + 7) / 8];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  void* wl = (char*)lds + wave * M::kLds;
-  dev::level_items(FR, ws, level, [&](int f, int q) {
-    const FrameDev& fr = FR.f[f];
-    const typename M::State st = M::frame_state(ws, fr, lane);
-    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
-    M::run_item(P, fr, ws, dbg, f, level, r, wave, lane, wl, st);
-  });
-}
-
-// Both levels with a vertical range in one launch: work items of every frame's close
-// level first, then of every far level (as match_pair_kernel), each wave with an LDS
-// share of wave_bytes (the larger of the two levels' needs). The two levels' blocks
-// overlap on the GPU, which outweighs the registers the combined kernel takes (measured
-// against one launch per level).
-template <int FROWS, int CROWS>
-__global__ __launch_bounds__(256) void match_dy_pair_kernel(MatchParamsDev P, FramesDev FR, MatchWs ws,
-                                                            DebugDev dbg, int wave_bytes) {
-  extern __shared__ uint64_t dy_lds[];
-  __shared__ int prefix[2 * kMaxFrames + 1];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  const int F = FR.n;
-  if (threadIdx.x < 64) {
-    // prefix[j]: items before slot j; slot j < F is frame j's close level, else frame
-    // j - F's far level
-    const int j = lane < F ? lane : lane - F;
-    const int cnt = lane < 2 * F ? ws.fcount[j * FC_N + (lane < F ? FC_CLOSE_ITEMS : FC_FAR_ITEMS)] : 0;
-    const int incl = dev::wave_incl_scan(cnt);
-    if (lane < 2 * F) prefix[lane + 1] = incl;
-    if (lane == 0) prefix[0] = 0;
-  }
-  __syncthreads();
-  void* wl = (char*)dy_lds + (size_t)wave * wave_bytes;
-  const int total = prefix[2 * F];
-  for (int m = blockIdx.x; m < total; m += gridDim.x) {
-    int slot = 0;
-    for (int k = 1; k < 2 * F; ++k)
-      if (m >= prefix[k]) slot = k;
-    const int f = slot < F ? slot : slot - F;
-    const FrameDev& fr = FR.f[f];
-    const int q = m - prefix[slot];
-    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, slot < F ? 1 : 0, q, lane);
-    if constexpr (FROWS == CROWS) {
-      // one matcher for both levels: a single inlined copy keeps the register count of
-      // the one-level kernel
-      dev::run_item_rec(P, fr, f, slot < F ? 1 : 0, r, wave, [&](const dev::BlockCtx& c) {
-        dev::match_block_dy<CROWS, CROWS>(P, fr, ws, dbg, c, lane, wl);
-      });
-    } else if (slot < F) {
-      dev::run_item_rec(P, fr, f, 1, r, wave, [&](const dev::BlockCtx& c) {
-        dev::match_block_dy<CROWS, CROWS>(P, fr, ws, dbg, c, lane, wl);
-      });
-    } else {
-      dev::run_item_rec(P, fr, f, 0, r, wave, [&](const dev::BlockCtx& c) {
-        dev::match_block_dy<FROWS, FROWS>(P, fr, ws, dbg, c, lane, wl);
       });
     }
   }
@@ -573,25 +449,7 @@ hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (P.vertical) {
-    // both levels in one launch; when both fit the wider matcher (ROWS = 8, which also
-    // takes 4 x 4 blocks, half its lanes idle) it serves both levels
-    int fr_rows = dy_rows(P.path[0].bw, P.path[0].bh), cr_rows = dy_rows(P.path[1].bw, P.path[1].bh);
-    auto fits8 = [](const PathDev& ph) {
-      return dy_strip_words(8, ph.nd) <= 64 * dy_chunks(8) &&
-             kItemWaves * dy_wave_lds_bytes(8, ph.nd, ph.ndy) <= kDyMaxWgLds;
-    };
-    if (fr_rows != cr_rows && fits8(P.path[0]) && fits8(P.path[1])) fr_rows = cr_rows = 8;
-    const size_t wave_bytes = std::max(dy_wave_lds_bytes(fr_rows, P.path[0].nd, P.path[0].ndy),
-                                       dy_wave_lds_bytes(cr_rows, P.path[1].nd, P.path[1].ndy));
-    const size_t bytes = kItemWaves * wave_bytes;
-    if (bytes > kDyMaxWgLds) return hipErrorInvalidValue;   // rejected by the argument checks
-    const int wb = (int)wave_bytes;
-    auto kernel = fr_rows == 4 && cr_rows == 8   ? match_dy_pair_kernel<4, 8>
-                  : fr_rows == 8 && cr_rows == 8 ? match_dy_pair_kernel<8, 8>
-                  : fr_rows == 4 && cr_rows == 4 ? match_dy_pair_kernel<4, 4>
-                                                 : match_dy_pair_kernel<8, 4>;
-    e = timed_launch(timer, "match", kernel, dim3(n_match_wgs), dim3(256), bytes, stream, P, FR, ws,
-                     dbg, wb);
+    e = launch_match_vertical(P, FR, ws, dbg, n_match_wgs, stream, timer);
     if (e != hipSuccess) return e;
   } else if (!dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd &&
              (level_launches == 2 || (level_launches == 0 && FR.n == 1)) &&

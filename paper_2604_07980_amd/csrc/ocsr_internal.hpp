@@ -76,22 +76,19 @@ struct MatchParamsDev {
                                    // the groups one wave takes
   int32_t full_census;             // whole-frame calls: 1 = census of every tile, 0 = only
                                    // of the tiles some box's search reads
-  int32_t vertical;                // 1: a vertical range is searched (the dy kernels run)
+  int32_t vertical;                // 1: a vertical range is searched
 };
 
-// Kernel of a path with a vertical range: one wave per block, NX x ROWS points, lanes
-// (row, group of dy_cpl(ROWS) consecutive candidates), the candidates in runtime passes
-// of kDyPass; per wave an LDS ring of ROWS + 1 strip rows of dy_strip_words words (each
-// vertical step loads one new row), the template, and the forward and backward costs of
-// every (d, dy) as uint16. A strip row is loaded in at most dy_chunks(ROWS) 64-word
-// chunks per lane.
+// What a path with a vertical range may ask for: nd level disparities x ndy vertical offsets
+// whose strip rows, template and two cost tables of 16 bits take at most a quarter of 64 KB
+// (a wave's LDS in a matcher that stages every strip row), its strip rows (padded to passes
+// of kDyPass candidates) at most dy_chunks 64-word loads. A documented limit of the entry
+// points, independent of the kernels that serve such a path now.
 constexpr int kDyPass = 32;
 inline int dy_rows(int bw, int bh) { return bw <= 4 && bh <= 4 ? 4 : 8; }
-constexpr int dy_cpl(int rows) { return rows == 4 ? 2 : 4; }
 constexpr int dy_chunks(int rows) { return rows == 4 ? 5 : 3; }
 constexpr int dy_strip_words(int rows, int nd) { return (nd + kDyPass - 1) / kDyPass * kDyPass + rows - 1; }
-// When all ROWS + ndy - 1 strip rows of a direction fit kDyFullLoads loads per lane they
-// are staged at once (one round trip), else the ring of ROWS + 1 rows is used.
+// (all ROWS + ndy - 1 strip rows where they fit 16 words per lane, else a ring of ROWS + 1)
 constexpr int kDyFullLoads = 16;
 constexpr bool dy_full(int rows, int nd, int ndy) {
   return (rows + ndy - 1) * dy_strip_words(rows, nd) <= 64 * kDyFullLoads;
@@ -102,7 +99,7 @@ inline size_t dy_wave_lds_bytes(int rows, int nd, int ndy) {
   return r16(sizeof(uint64_t) * dy_lds_rows(rows, nd, ndy) * dy_strip_words(rows, nd)) +
          r16(sizeof(uint64_t) * rows * rows) + 2 * r16(sizeof(uint16_t) * (size_t)nd * ndy);
 }
-constexpr size_t kDyMaxWgLds = 65536;   // LDS of one dy workgroup (kItemWaves waves)
+constexpr size_t kDyMaxWgLds = 65536;
 
 // One frame of a call: descriptor levels, its boxes and (whole-frame calls) its images.
 struct FrameDev {
@@ -267,6 +264,11 @@ hipError_t launch_match(const MatchParamsDev& p, const FramesDev& fr, const ocsr
                         const MatchWs& ws, ocsr_box_result* out, const DebugDev& dbg,
                         bool plan_done, int n_match_wgs, int level_launches, hipStream_t stream,
                         const LaunchTimer* timer);
+
+// The matching launches of a call with a vertical range.
+hipError_t launch_match_vertical(const MatchParamsDev& p, const FramesDev& fr, const MatchWs& ws,
+                                 const DebugDev& dbg, int n_match_wgs, hipStream_t stream,
+                                 const LaunchTimer* timer);
 
 // Fused path: census of every frame, planning, matching and aggregation in one
 // persistent launch of co-resident workgroups (after a counter reset). Returns

@@ -50,3 +50,27 @@ def test_matrix_matcher(lib, orc, path, related):
     _check_debug(lib, extra, blk, cf, cb, n)
     plain = lib.match_boxes(*g, _cuda(boxes), p, cap_blocks=max(n, 1) + 3)
     assert (plain == out).all()         # the kernels without debug output
+
+
+@pytest.mark.parametrize("dy", [(-2, 3), (-6, -1)], ids=lambda d: f"dy{d[0]}_{d[1]}")
+@pytest.mark.parametrize("path", [(8, 8, 0, 31), (8, 8, 1, 96), (8, 8, 0, 127), (8, 8, 0, 159), (5, 7, 0, 40),
+                                  (4, 4, 0, 31), (4, 4, 0, 63), (4, 4, 0, 100), (3, 2, 5, 9)],
+                         ids=lambda p: f"{p[0]}x{p[1]}_d{p[2]}-{p[3]}")
+def test_matrix_matcher_vertical(lib, orc, path, dy):
+    """The same over a vertical range: unrelated views (every group's blocks at offsets of
+    their own) and boxes whose strips leave the image above and below."""
+    bw, bh, dmin, dmax = path
+    rng = np.random.default_rng(bw * 1000 + bh * 100 + dmax + dy[0])
+    left, right = (rng.integers(0, 256, (H, W), dtype=np.uint8) for _ in range(2))
+    right[:, :W // 2] = synth.drift_rows(left, dy[1])[:, W // 8:W // 8 + W // 2]
+    boxes = _boxes(rng)
+    p = synth.base_params()
+    p.update(tau_s=1 << 20, min_point_pct=30, dy_min=dy[0], dy_max=dy[1])
+    p["far"] = dict(mode=0, bw=bw, bh=bh, n_side=8, dmin=dmin, dmax=dmax)
+    p["close"] = dict(p["close"], dmax=31)
+    _, (res, blk, cf, cb, n) = orc.run_scene(left, right, p, boxes, debug=True)
+    g = _gpu_levels(lib, left, right, p)
+    out, extra = lib.match_boxes(*g, _cuda(boxes), p, debug=True, cap_blocks=max(n, 1) + 3)
+    assert_results_match(lib.results_to_numpy(out), res)
+    _check_debug(lib, extra, blk, cf, cb, n)
+    assert (lib.match_boxes(*g, _cuda(boxes), p, cap_blocks=max(n, 1) + 3) == out).all()
