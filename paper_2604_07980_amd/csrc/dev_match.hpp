@@ -583,45 +583,65 @@ __device__ __forceinline__ void box_candidates(OccLanes& oc, int n, int k, int l
 // ---------------------------------------------------------------------------------
 // Any block of up to 64 points on any point grid (TILED, or the single GRID block of
 // the paper's far path, Sec. 4.3.4 "Far Objects"), up to 256 candidates: one wave per
-// block, lane l takes candidates l + 64 r (r < 4) and walks the block's unmasked points
-// one at a time. A point's template word is the same for every lane; its candidate
-// words are consecutive in the row, one per lane. Every read of the level images goes
-// through ld_word, which returns 0 outside [0, W); point rows lie inside the level box.
+// block. The kept points are listed in LDS (template word, offset and column); lane l takes
+// candidate l (and l + 64, ..), and with at most 32 (16) candidates the wave's halves
+// (quarters) share the points out. Each step loads eight points' candidate words before
+// it uses any: a GRID level has few blocks, one per far box, and a wave that waits for
+// each of 64 points in turn was all its time (48 boxes of a
+// 1080p frame, both levels: 53 us, now 18).
+// Reads of the level images are checked against [0, W); point rows lie inside the level
+// box.
 // ---------------------------------------------------------------------------------
-constexpr size_t kGenericLdsBytes = sizeof(uint32_t) * 2 * 256;
+struct GenericLds {
+  uint32_t costf[256], costb[256];
+  uint64_t tmpl[64 + 8];      // the listed points' template words; 0 past the end
+  int64_t row[64 + 8];        // their row's first word
+  int32_t x[64 + 8];          // their column (forward) or match column (backward)
+};
+constexpr size_t kGenericLdsBytes = sizeof(GenericLds);
 
-__device__ __forceinline__ void generic_costs(const LevelDev& lv, const BlockGeom& g, uint64_t mask,
-                                              int dlo, int nd, bool fwd, int d_f, int lane,
+// acc[r]: the cost of candidate l + 64 r over the n listed points, l = lane mod (64 / ng).
+// Candidate kc of a point reads column x + step (dlo + kc) of img.
+__device__ __forceinline__ void generic_costs(const GenericLds& sm, const uint64_t* __restrict__ img, int W,
+                                              int n, int dlo, int nd, int step, int ng, int lane,
                                               uint32_t (&acc)[4]) {
+  constexpr int B = 8;
+  const int per = 64 / ng, l = lane & (per - 1), grp = lane / per;
   acc[0] = acc[1] = acc[2] = acc[3] = 0;
-  uint64_t m = mask;
-  while (m) {
-    const int t = __ffsll((unsigned long long)m) - 1;
-    m &= m - 1;
-    const int j = t / g.nx, i = t - j * g.nx;
-    const int x = geom_col(g, i), y = geom_row(g, j);
-    const uint64_t* __restrict__ rowL = lv.L + (size_t)y * lv.pitch;
-    const uint64_t* __restrict__ rowR = lv.R + (size_t)y * lv.pitch;
-    // forward: CL(x) against CR(x - d); backward: CR(x - d_f) against CL(x - d_f + d')
-    const uint64_t tmpl = fwd ? ld_word(rowL, x, lv.W) : ld_word(rowR, x - d_f, lv.W);
-    const uint64_t* __restrict__ other = fwd ? rowR : rowL;
+  for (int i0 = 0; i0 < n; i0 += B * ng) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int kc = lane + 64 * r;
-      const int xc = fwd ? x - (dlo + kc) : x - d_f + dlo + kc;
-      if (kc < nd) acc[r] = popc64_acc(tmpl ^ ld_word(other, xc, lv.W), acc[r]);
+      if (64 * r >= nd) break;   // wave-uniform
+      const int kc = l + 64 * r;
+      const int dx = step * (dlo + kc);
+      uint64_t w[B], t[B];
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const int i = min(i0 + j * ng + grp, n);      // entry n: a word that differs from none
+        const int xc = sm.x[i] + dx;
+        const bool ok = kc < nd && i < n && xc >= 0 && xc < W;
+        t[j] = sm.tmpl[i];
+        w[j] = img[ok ? sm.row[i] + xc : 0];
+        w[j] = ok ? w[j] : 0ull;
+      }
+#pragma unroll
+      for (int j = 0; j < B; ++j) acc[r] = popc64_acc(t[j] ^ w[j], acc[r]);
     }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (ng >= 2) acc[r] += (uint32_t)__shfl_xor((int)acc[r], 32, 64);
+    if (ng == 4) acc[r] += (uint32_t)__shfl_xor((int)acc[r], 16, 64);
   }
 }
 
 __device__ __forceinline__ void match_block_generic(const MatchParamsDev& P, const FrameDev& fr,
                                                     const MatchWs& ws, const DebugDev& dbg,
                                                     const BlockCtx& c, int lane, void* lds) {
-  uint32_t* costf = (uint32_t*)lds;
-  uint32_t* costb = costf + 256;
+  GenericLds& sm = *(GenericLds*)lds;
   const LevelDev& lv = fr.lv[c.level];
   const PathDev& ph = P.path[c.level];
-  const int nd = ph.nd, dlo = ph.dlo;
+  const int nd = ph.nd, dlo = ph.dlo, W = lv.W;
   const uint64_t mask = block_mask(ws, fr.box_off, fr.n_boxes, c.k, c.g, lane);
   const bool eligible = block_eligible(P, mask, c.g.nx * c.g.ny);
   if (!eligible) {
@@ -629,32 +649,59 @@ __device__ __forceinline__ void match_block_generic(const MatchParamsDev& P, con
     wave_sync();
     return;
   }
+  // the kept points' list: lane t's point (t mod nx, t / nx) at its rank in the mask
+  const int n = (int)__popcll(mask);
+  const bool kept = (mask >> lane) & 1ull;
+  const int at = (int)__popcll(mask & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
+  const int pj = lane / c.g.nx, pi = lane - pj * c.g.nx;
+  const int px = kept ? geom_col(c.g, pi) : 0;
+  const int64_t prow = kept ? (int64_t)geom_row(c.g, pj) * lv.pitch : 0;
+  if (kept) {
+    sm.tmpl[at] = ld_word(lv.L + prow, px, W);
+    sm.row[at] = prow;
+    sm.x[at] = px;
+  }
+  if (lane == 0) {
+    sm.tmpl[n] = 0;
+    sm.row[n] = 0;
+    sm.x[n] = 0;
+  }
+  wave_sync();
+  const int ng = nd <= 16 ? 4 : nd <= 32 ? 2 : 1;
+  const bool lead = lane < 64 / ng;             // one lane per candidate
   uint32_t acc[4];
-  generic_costs(lv, c.g, mask, dlo, nd, true, 0, lane, acc);
+  // forward: CL(x) against CR(x - d)
+  generic_costs(sm, lv.R, W, n, dlo, nd, -1, ng, lane, acc);
   uint32_t key = 0xFFFFFFFFu;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int kc = lane + 64 * r;
-    if (kc < nd) {
+    if (lead && kc < nd) {
       key = min(key, (acc[r] << 16) | (uint32_t)kc);
-      costf[kc] = acc[r];
+      sm.costf[kc] = acc[r];
     }
   }
   key = wave_min_dpp(key);
   const int best = (int)(key & 0xFFFFu);
   const int d_f = dlo + best;
   wave_sync();
-  const int ca = (int)costf[max(best - 1, 0)];
-  const int cb = (int)costf[min(best + 1, nd - 1)];
+  const int ca = (int)sm.costf[max(best - 1, 0)];
+  const int cb = (int)sm.costf[min(best + 1, nd - 1)];
   const float d_sub = subpixel(d_f, best, nd, ca, (int)(key >> 16), cb);
-  generic_costs(lv, c.g, mask, dlo, nd, false, d_f, lane, acc);
+  // backward: CR(x - d_f) against CL(x - d_f + d')
+  if (kept) {
+    sm.tmpl[at] = ld_word(lv.R + prow, px - d_f, W);
+    sm.x[at] = px - d_f;
+  }
+  wave_sync();
+  generic_costs(sm, lv.L, W, n, dlo, nd, 1, ng, lane, acc);
   uint32_t bkey = 0xFFFFFFFFu;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int kc = lane + 64 * r;
-    if (kc < nd) {
+    if (lead && kc < nd) {
       bkey = min(bkey, (acc[r] << 16) | (uint32_t)kc);
-      costb[kc] = acc[r];
+      sm.costb[kc] = acc[r];
     }
   }
   bkey = wave_min_dpp(bkey);
@@ -663,8 +710,8 @@ __device__ __forceinline__ void match_block_generic(const MatchParamsDev& P, con
   if (c.b < dbg.cap_blocks && (dbg.cost_fwd || dbg.cost_bwd)) {
     wave_sync();
     for (int kc = lane; kc < nd && kc < dbg.cap_nd; kc += 64) {
-      if (dbg.cost_fwd) dbg.cost_fwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)costf[kc];
-      if (dbg.cost_bwd) dbg.cost_bwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)costb[kc];
+      if (dbg.cost_fwd) dbg.cost_fwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)sm.costf[kc];
+      if (dbg.cost_bwd) dbg.cost_bwd[(size_t)c.b * dbg.cap_nd + kc] = (uint16_t)sm.costb[kc];
     }
   }
   write_block(ws, dbg, c, ph, mask, true, d_f, d_b, lr_ok, d_sub, lr_ok, lane);
@@ -1300,7 +1347,7 @@ struct TiledMatcher {
 };
 // any block of up to 64 points (GRID blocks included), lanes over candidates
 struct GenericMatcher {
-  static constexpr size_t kLds = kGenericLdsBytes;
+  static constexpr size_t kLds = (kGenericLdsBytes + 15) & ~(size_t)15;
   using State = NoFrameState;
   static __device__ __forceinline__ State frame_state(const MatchWs&, const FrameDev&, int) { return {}; }
   static __device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr,
