@@ -1,14 +1,16 @@
 // Census transform of one 64 x 32 tile of level pixels by one workgroup of 256
 // threads (Sec. 4.3.1: census equation and Alg. 1).
 //
-// The tile plus its halo is staged in LDS as vertical pixel pairs (two 8-bit samples
-// in the two 16-bit halves of a word). Each lane owns one column and eight rows (four
-// pairs) and keeps the pair words of its window in registers. One packed 16-bit
-// subtract (centre pair - neighbour pair) decides a comparison for both pixels of a
-// pair: a half is >= 0xFF01 exactly when the neighbour is brighter, so its bits 8..15
-// all carry the comparison bit and one AND-OR drops both bits into place in a
-// byte-per-code-byte accumulator. Byte permutes then assemble the two 64-bit codes:
-// about one VALU instruction per comparison bit, with no lane-mask traffic.
+// The tile plus its halo is staged in LDS as bytes. Each lane owns four horizontally
+// adjacent pixels of two rows, a pixel per byte of a word, and compares four at once:
+// v_lerp_u8 of a neighbour word and the complemented centre word, (n + 255 - c) >> 1 in
+// every byte, has bit 7 set exactly where the neighbour is brighter. A shift and a bit-field
+// insert file the four bits in a running word, eight comparisons to a byte of the code, and
+// byte permutes put the eight bytes of each pixel's code together: three VALU instructions
+// for four comparisons, counted over the kernel 1.10 per comparison, against 1.28 with
+// 16-bit subtracts of two pixels. Both the VALU (10.5 us of it for a 1080p pair at two
+// levels) and the stores (8.5 us for its 42 MB at the rate of a fill) bound it: the pair takes
+// 15.8 us (17.1 with the subtracts), the 138 MB of 16 listed 1200p frames 48.8 us (54.5).
 //
 // Bit order: Alg. 1 starts from the sentinel and, for i = -SX..SX (x, outer) and
 // j = -SY..SY (y, inner), shifts left and appends [I(x+i, y+j) > I(x, y)]; the first
@@ -21,16 +23,21 @@
 namespace ocsr {
 namespace dev {
 
-constexpr int kCensusRowsPerLane = 8;   // 4 waves x 8 rows = kCensusTileY
+constexpr int kCensusRowsPerLane = 2;   // 4 waves x 4 lane groups x 2 rows = kCensusTileY
 
 template <int SX, int SY>
 struct CensusTile {
-  static constexpr int LW = kCensusTileX + 2 * SX;
-  static constexpr int PR = kCensusTileY + 2 * SY - 1;            // rows of pixel pairs
-  static constexpr int WR = kCensusRowsPerLane - 1 + 2 * SY;      // pair rows per lane
+  static constexpr int LW = (kCensusTileX + 2 * SX + 3) / 4;      // words of a staged row
+  static constexpr int LP = 24;                                   // LDS words per row: the four lane
+                                                                  // groups of a wave, two rows
+                                                                  // apart, read different banks
+  static constexpr int LR = kCensusTileY + 2 * SY;                // staged rows
   static constexpr int N = (2 * SX + 1) * (2 * SY + 1);           // comparisons
-  static constexpr size_t kLdsBytes = sizeof(uint32_t) * (PR * LW + 64);   // + spare words
+  // the staged tile, then 512 words per wave in which a row of codes changes lanes
+  static constexpr int kOutAt = LP * LR;
+  static constexpr size_t kLdsBytes = sizeof(uint32_t) * (kOutAt + 4 * 512);
   static_assert(N + 1 <= 64, "window wider than a 64-bit code");
+  static_assert(SX <= 4 && LW <= LP, "a lane's window row is at most three words");
 };
 
 // One census tile: the uint8 source img (pitch bytes, W x H) at level scale s (level
@@ -43,181 +50,196 @@ struct CensusJob {
   int out_pitch, X0, Y0;
 };
 
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-// P[r * LW + c] = I(c, r) | I(c, r + 1) << 16 over the tile and its halo (level
-// samples, c and r counted from the halo's corner). A position outside the level image
-// reads some valid byte of the image instead: only pixels whose window leaves the image
-// see such values, and their words are stored as 0 regardless.
+// Word (r, c) of the staged tile is level samples 4c .. 4c + 3 of row r, counted from the
+// halo's corner. A position outside the level image reads some valid byte of the image
+// instead: only pixels whose window leaves the image see such values, and their words are
+// stored as 0 regardless.
 __device__ __forceinline__ int clamp_to(int v, int n) { return v < 0 ? 0 : (v < n ? v : n - 1); }
 
-// Stages tile j in P through registers. For the first 64 columns wave w loads source rows
-// w*RB .. w*RB + RB of the tile (one more than the pair rows it writes): the row address
-// is wave-uniform, so each load is one scalar base plus the lane's unsigned column
-// offset. The 2 SX halo columns to their right take one pair word per thread. All loads
-// are issued before the first is waited for. census_load issues them into registers and
-// census_put writes those to P, so that a caller can keep one tile's loads in flight
-// while it works on another; census_stage does both. Called by all 256 threads of the
-// workgroup.
+// y moved down by one bit with bit 7 of every byte of x on top: two instructions. m: 0x80808080
+// in a vector register (v_bitop3_b32 and right shifts issue up to 1.6 times as fast as
+// other three-operand instructions, but only without scalar operands). As asm: free to
+// reassociate the builtin, the compiler takes 84 registers instead of 50 and loses half the
+// waves.
+__device__ __forceinline__ uint32_t push_bits(uint32_t y, uint32_t x, uint32_t m) {
+  uint32_t r;                                   // m ? x : y >> 1
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xca" : "=v"(r) : "v"(m), "v"(x), "v"(y >> 1));
+  return r;
+}
+
+// Whether tile j's samples are read as words (level scales 1 and 2): every staged sample, and
+// four more to the right, lies inside the level image. Uniform over the workgroup.
 template <int SX, int SY>
-struct CensusRegs {
+__device__ __forceinline__ bool census_words(const CensusJob& j) {
   using T = CensusTile<SX, SY>;
-  static constexpr int RB = (T::PR + 1 + 3) / 4;
-  static constexpr int NX = T::LW - 64, NH = (NX * T::PR + 255) / 256;
-  static_assert(NX > 0 && NX <= 64, "one pass of 64 columns, then the halo columns");
-  uint32_t px[RB + 1];
-  uint32_t hlo[NH], hhi[NH];
-};
-
-template <int SX, int SY>
-__device__ __forceinline__ void census_load(const CensusJob& j, CensusRegs<SX, SY>& g) {
-  using G = CensusRegs<SX, SY>;
-  constexpr int PR = G::T::PR, RB = G::RB, NX = G::NX, NH = G::NH;
-  const uint8_t* img = uniform(j.img);
-  const int pitch = uniform(j.pitch), s = uniform(j.s);
-  const int X0 = uniform(j.X0), Y0 = uniform(j.Y0);
-  const int Ws = uniform(j.Ws), Hs = uniform(j.Hs);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  // each row through a buffer resource over that row (scalar setup), the lane's clamped
-  // column a byte offset fixed for the tile: no per-load address arithmetic
-  const uint32_t coff = (uint32_t)(s * clamp_to(X0 - SX + lane, Ws));
-  const int wbytes = uniform(j.W);
-#pragma unroll
-  for (int k = 0; k <= RB; ++k) {
-    const int Yc = clamp_to(Y0 - SY + wave * RB + k, Hs);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(img + (size_t)(s * Yc) * pitch), (short)0, wbytes, 0x00020000);
-    g.px[k] = __builtin_amdgcn_raw_buffer_load_b8(rs, coff, 0, 0);
-  }
-  // halo word t = pr NX + (pc - 64): its two source bytes through per-thread addresses
-  // (threads past the halo load the last row's word again and store it to the spare
-  // words)
-#pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    const int t = (int)threadIdx.x + 256 * i;
-    const int pr = min(t / NX, PR - 1);
-    const int pc = 64 + t % NX;
-    const size_t col = (size_t)(s * clamp_to(X0 - SX + pc, Ws));
-    g.hlo[i] = img[(size_t)(s * clamp_to(Y0 - SY + pr, Hs)) * pitch + col];
-    g.hhi[i] = img[(size_t)(s * clamp_to(Y0 - SY + pr + 1, Hs)) * pitch + col];
-  }
+  return uniform(j.s <= 2 && j.X0 >= SX && j.X0 - SX + 4 * T::LW + 4 <= j.Ws && j.Y0 >= SY &&
+                 j.Y0 - SY + T::LR <= j.Hs) != 0;
 }
 
-template <int SX, int SY>
-__device__ __forceinline__ void census_put(const CensusRegs<SX, SY>& g, uint32_t* P) {
-  using G = CensusRegs<SX, SY>;
-  constexpr int LW = G::T::LW, PR = G::T::PR, RB = G::RB, NX = G::NX, NH = G::NH;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int k = 0; k < RB; ++k) {
-    const int pr = wave * RB + k;   // wave-uniform: the test is a scalar branch
-    if (pr < PR) P[pr * LW + lane] = g.px[k] | (g.px[k + 1] << 16);
-  }
-#pragma unroll
-  for (int i = 0; i < NH; ++i) {
-    const int t = (int)threadIdx.x + 256 * i;
-    P[t < NX * PR ? (t / NX) * LW + 64 + t % NX : PR * LW + lane] = g.hlo[i] | (g.hhi[i] << 16);
-  }
-}
-
+// Stages tile j in P. A tile of words takes eight unaligned bytes per staged word (at scale 1
+// the first four are the word, at scale 2 the even ones); the others (on the image's border,
+// or at other scales) a clamped byte per sample. All loads are issued before the first is
+// waited for. Called by all 256 threads of the workgroup.
 template <int SX, int SY>
 __device__ __forceinline__ void census_stage(const CensusJob& j, uint32_t* P) {
-  CensusRegs<SX, SY> g;
-  census_load<SX, SY>(j, g);
-  census_put<SX, SY>(g, P);
+  using T = CensusTile<SX, SY>;
+  constexpr int NT = T::LW * T::LR, NW = (NT + 255) / 256;
+  const int s = uniform(j.s);
+  const int64_t pitch = (int64_t)s * uniform(j.pitch);   // of a level row
+  const uint8_t* img = uniform(j.img);
+  const int X0 = uniform(j.X0) - SX, Y0 = uniform(j.Y0) - SY;
+  // thread t stages the words t, t + 256, .. (threads past the tile its last word again)
+  if (census_words<SX, SY>(j)) {
+    const uint8_t* corner = img + Y0 * pitch + s * X0;
+    const uint32_t sel = s == 1 ? 0x03020100u : 0x06040200u;
+    uint64_t w[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int t = min((int)threadIdx.x + 256 * i, NT - 1);
+      const int r = t / T::LW, c = t - r * T::LW;
+      __builtin_memcpy(&w[i], corner + r * pitch + 4 * s * c, 8);
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int t = min((int)threadIdx.x + 256 * i, NT - 1);
+      const int r = t / T::LW, c = t - r * T::LW;
+      P[r * T::LP + c] = __builtin_amdgcn_perm((uint32_t)(w[i] >> 32), (uint32_t)w[i], sel);
+    }
+  } else {
+    const int Ws = uniform(j.Ws), Hs = uniform(j.Hs);
+    uint32_t b[NW][4];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int t = min((int)threadIdx.x + 256 * i, NT - 1);
+      const int r = t / T::LW, c = t - r * T::LW;
+      const uint8_t* row = img + clamp_to(Y0 + r, Hs) * pitch;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) b[i][k] = row[s * clamp_to(X0 + 4 * c + k, Ws)];
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int t = min((int)threadIdx.x + 256 * i, NT - 1);
+      const int r = t / T::LW, c = t - r * T::LW;
+      P[r * T::LP + c] = b[i][0] | (b[i][1] << 8) | (b[i][2] << 16) | (b[i][3] << 24);
+    }
+  }
 }
 
 // The census words of tile j from P (staged by census_stage), after a barrier. Called
 // by all 256 threads of the workgroup.
 template <int SX, int SY>
-__device__ __forceinline__ void census_compute(const CensusJob& j, int sentinel, const uint32_t* P) {
+__device__ __forceinline__ void census_compute(const CensusJob& j, int sentinel, uint32_t* P) {
   using T = CensusTile<SX, SY>;
-  constexpr int LW = T::LW, WR = T::WR, N = T::N;
+  constexpr int R = kCensusRowsPerLane, LP = T::LP, N = T::N;
+  constexpr int WR = R + 2 * SY;                // staged rows a lane reads
   uint64_t* out = uniform(j.out);
-  const int s = uniform(j.s), out_pitch = uniform(j.out_pitch);
+  const int out_pitch = uniform(j.out_pitch);
   const int X0 = uniform(j.X0), Y0 = uniform(j.Y0);
   const int Ws = uniform(j.Ws), Hs = uniform(j.Hs);
-  const int lane = threadIdx.x & 63;
-  const int r0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * kCensusRowsPerLane;
-  uint64_t* orow = uniform(out + (size_t)(Y0 + r0) * out_pitch);   // the wave's first row
-  // the lane's window words are read one window column at a time, so that only one
-  // column (WR words) is held besides the accumulators
-  const uint32_t* Pl = P + r0 * LW + lane;
-  const int X = X0 + lane;
-  const bool x_in = X < Ws;
-  const bool x_def = X >= SX && X < Ws - SX;
-  constexpr int NP = kCensusRowsPerLane / 2;
-  static_assert(NP == 2 || NP == 4, "the accumulation barrier below names two or four pairs");
-  // pair pp holds pixels A = (X, Y0 + r0 + 2pp) and B = (X, YA + 1) in its low / high half
-  uint32_t acc[NP][8];
-  u16x2 c2[NP];
+  const int tid = threadIdx.x;
+  const int col = tid & 15, r0 = R * (tid >> 4);
+  // the lane's window: words col .. col + 2 of WR rows (bytes 0 .. 3 + 2 SX)
+  uint32_t d[WR][3];
+  const uint32_t* Pl = P + r0 * LP + col;
 #pragma unroll
-  for (int pp = 0; pp < NP; ++pp) {
+  for (int r = 0; r < WR; ++r)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[pp][k] = 0;
-    c2[pp] = __builtin_bit_cast(u16x2, Pl[(2 * pp + SY) * LW + SX]);
+    for (int k = 0; k < 3; ++k) d[r][k] = 4 * k < 4 + 2 * SX ? Pl[r * LP + k] : 0u;
+  const uint32_t m = in_vgpr(0x80808080u);
+  const bool inside = X0 >= SX && X0 + kCensusTileX <= Ws - SX && Y0 >= SY && Y0 + kCensusTileY <= Hs - SY;
+  // four pixels of staged row r, i columns right of the window's left edge
+  auto window = [&](int r, int i) {
+    return (i & 3) == 0 ? d[r][i >> 2] : __builtin_amdgcn_alignbyte(d[r][min((i >> 2) + 1, 2)], d[r][i >> 2], i & 3);
+  };
+  uint32_t nc[R];                               // the complemented centres
+#pragma unroll
+  for (int k = 0; k < R; ++k) nc[k] = ~window(SY + k, SX);
+  // code byte q of the four pixels of each row; y collects a byte's bits from bit 7 down:
+  // each new one goes to bit 7 after the others moved down (what crosses into the next
+  // pixel's bit 7 is overwritten by the same step). Window column by window column for both
+  // rows, which share the shifted words (row by row they stay in 40 more registers).
+  uint32_t code[R][8], y[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    y[k] = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) code[k][q] = 0;
   }
 #pragma unroll
-  for (int i = 0; i < 2 * SX + 1; ++i) {
+  for (int i = 2 * SX; i >= 0; --i) {
     uint32_t v[WR];
 #pragma unroll
-    for (int rr = 0; rr < WR; ++rr) v[rr] = Pl[rr * LW + i];
+    for (int r = 0; r < WR; ++r) v[r] = window(r, i);
 #pragma unroll
-    for (int jj = 0; jj < 2 * SY + 1; ++jj) {
-      // the centre against itself: its bit is 0, nothing to file
-      if (i == SX && jj == SY) continue;
+    for (int jj = 2 * SY; jj >= 0; --jj) {
       const int pos = N - 1 - (i * (2 * SY + 1) + jj);   // Alg. 1 order, MSB first
-      const int q = pos >> 3;
-      uint32_t d[NP];
 #pragma unroll
-      for (int pp = 0; pp < NP; ++pp) {
-        // half = centre - neighbour: in 0..255 when the neighbour is not brighter, in
-        // 0xFF01..0xFFFF when it is, so bits 8..15 of each half all equal the bit
-        d[pp] = __builtin_bit_cast(uint32_t, c2[pp] - __builtin_bit_cast(u16x2, v[2 * pp + jj]));
+      for (int k = 0; k < R; ++k) {
+        if (i == SX && jj == SY) {              // the centre against itself: its bit is 0
+          y[k] = (pos & 7) == 0 ? 0u : (y[k] >> 1) & 0x7F7F7F7Fu;
+        } else {
+          const uint32_t x = __builtin_amdgcn_lerp(v[jj + k], nc[k], 0u);
+          y[k] = (pos & 7) == 0 ? x : push_bits(y[k], x, m);
+        }
+        if ((pos & 7) == 7) code[k][pos >> 3] = y[k];
       }
-#pragma unroll
-      for (int pp = 0; pp < NP; ++pp) acc[pp][q] = (d[pp] & (0x01000100u << (pos & 7))) | acc[pp][q];
-      // One v_and_or_b32 per comparison and pair. The empty asm keeps the compiler from
-      // regrouping the ORs into v_or3_b32 trees (an extra v_and_b32 per bit); the four
-      // pairs' subtracts are issued ahead of their AND-ORs, so no packed-result wait
-      // state is needed.
-      if constexpr (NP == 4)
-        asm volatile("" : "+v"(acc[0][q]), "+v"(acc[1][q]), "+v"(acc[2][q]), "+v"(acc[3][q]));
-      else
-        asm volatile("" : "+v"(acc[0][q]), "+v"(acc[1][q]));
     }
   }
 #pragma unroll
-  for (int pp = 0; pp < NP; ++pp) {
-    if (sentinel) acc[pp][N >> 3] |= 0x01000100u << (N & 7);
-    // code byte k of A is byte 1 of acc[k], of B byte 3
-    const uint32_t x01 = __builtin_amdgcn_perm(acc[pp][1], acc[pp][0], 0x07030501u);
-    const uint32_t x23 = __builtin_amdgcn_perm(acc[pp][3], acc[pp][2], 0x07030501u);
-    const uint32_t x45 = __builtin_amdgcn_perm(acc[pp][5], acc[pp][4], 0x07030501u);
-    const uint32_t x67 = __builtin_amdgcn_perm(acc[pp][7], acc[pp][6], 0x07030501u);
-    const uint64_t codeA = ((uint64_t)__builtin_amdgcn_perm(x67, x45, 0x05040100u) << 32) |
-                           __builtin_amdgcn_perm(x23, x01, 0x05040100u);
-    const uint64_t codeB = ((uint64_t)__builtin_amdgcn_perm(x67, x45, 0x07060302u) << 32) |
-                           __builtin_amdgcn_perm(x23, x01, 0x07060302u);
-    // rows are wave-uniform: the row address steps by the pitch (scalar adds), the
-    // lane's column is an unsigned offset
-    const int YA = Y0 + r0 + 2 * pp;
-    const int YB = YA + 1;
-    if (YA < Hs && x_in) {
-      const bool def = x_def && YA >= SY && YA < Hs - SY;
-      orow[(uint32_t)X] = def ? codeA : 0ull;
+  for (int k = 0; k < R; ++k) {
+    // the sentinel above the last comparison, and the top byte's bits moved to its low end
+    {
+      constexpr int top = N & 7;                // the sentinel's bit
+      const uint32_t sb = sentinel ? 0x80808080u : 0u;
+      uint32_t t = top == 0 ? sb : sb | ((y[k] >> 1) & 0x7F7F7F7Fu);
+      if (top < 7) t = (t >> (7 - top)) & (0x01010101u * ((1u << (top + 1)) - 1u));
+      code[k][N >> 3] = t;
     }
-    orow += out_pitch;
-    if (YB < Hs && x_in) {
-      const bool def = x_def && YB >= SY && YB < Hs - SY;
-      orow[(uint32_t)X] = def ? codeB : 0ull;
+    // 4 x 4 byte transposes: word h of pixel p's code
+    uint32_t w[4][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t* c = code[k] + 4 * h;
+      const uint32_t a0 = __builtin_amdgcn_perm(c[1], c[0], 0x05010400u), a1 = __builtin_amdgcn_perm(c[1], c[0], 0x07030602u);
+      const uint32_t b0 = __builtin_amdgcn_perm(c[3], c[2], 0x05010400u), b1 = __builtin_amdgcn_perm(c[3], c[2], 0x07030602u);
+      w[0][h] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+      w[1][h] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+      w[2][h] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+      w[3][h] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
     }
-    orow += out_pitch;
+    if (inside) {
+      // through LDS, so that a store covers two whole rows of 512 bytes, 16 bytes a lane
+      // (straight from the lanes it would cover every other 16 bytes of four rows, which
+      // writes at 4.0 TB/s where whole rows reach 5.0)
+      const int lane = tid & 63, wave = tid >> 6;
+      uint32_t* o = P + T::kOutAt + wave * 512;
+      wave_sync();                              // the previous row is read
+      *(uint4*)(o + 8 * lane) = uint4{w[0][0], w[0][1], w[1][0], w[1][1]};
+      *(uint4*)(o + 8 * lane + 4) = uint4{w[2][0], w[2][1], w[3][0], w[3][1]};
+      wave_sync();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        // lane l holds 16 bytes of the wave's row group 2 h + l / 32
+        const uint4 v = *(const uint4*)(o + 256 * h + 4 * lane);
+        const int Y = Y0 + R * (4 * wave + 2 * h + (lane >> 5)) + k;
+        __builtin_memcpy(out + (size_t)Y * out_pitch + X0 + 2 * (lane & 31), &v, 16);
+      }
+    } else {
+      const int Y = Y0 + r0 + k, X = X0 + 4 * col;
+      if (Y < Hs) {
+        uint64_t* o = out + (size_t)Y * out_pitch + X;
+        const bool row_def = Y >= SY && Y < Hs - SY;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          if (X + p < Ws) {
+            const bool def = row_def && X + p >= SX && X + p < Ws - SX;
+            o[p] = def ? ((uint64_t)w[p][1] << 32) | w[p][0] : 0ull;
+          }
+        }
+      }
+    }
   }
 }
-
 
 // One tile, staged through registers.
 template <int SX, int SY>

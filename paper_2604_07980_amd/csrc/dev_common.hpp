@@ -16,6 +16,12 @@ __device__ __forceinline__ int cdiv_nonneg(int a, int s) {
 // A value the whole wave holds, moved to scalar registers (the compiler cannot always
 // tell that a value read through a uniformly computed index is uniform).
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// A constant held in a vector register: many instructions issue faster without a scalar
+// operand, and three-operand ones take no literals.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 // A pointer to global memory that the whole wave holds (the result stays a global-memory
 // pointer, so accesses through it remain global rather than flat instructions).
 template <class T>

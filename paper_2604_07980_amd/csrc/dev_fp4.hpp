@@ -27,12 +27,6 @@ __device__ __forceinline__ v4f mfma_fp4(v4i a, v4i b, v4f c) {
 
 // FP4 codes: the sign bit and, repeated eight times, the magnitudes 1, 2 and 4.
 constexpr uint32_t kSign = 0x88888888u, kOne = 0x22222222u, kTwo = 0x44444444u, kFour = 0x66666666u;
-// a constant in a vector register: v_and_or_b32 has no literals and one scalar operand
-__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 // 32 bits of a word as 32 numbers +-1 (bit 1: -1), seven instructions. sign, one: kSign and
 // kOne, or both 0 for a word whose terms do not count. p . q = 64 - 2 popcount(p ^ q).
 __device__ __forceinline__ v4i fp4_signs(uint32_t w, uint32_t sign, uint32_t one) {
