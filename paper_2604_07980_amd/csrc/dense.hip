@@ -22,18 +22,19 @@
 // step adds the products of the entering row and subtracts those of the leaving one (the
 // leaving row's signs flipped). The horizontal window runs along a diagonal: the neighbour
 // column in the next lane pairs with the next accumulator, so 2R wave-wide DPP adds of
-// packed pairs of 16-bit sums (at most 49 x 128) finish a window. A candidate's key is
-// 2 cost << 3 | rank in 16 bits, two to a word; packed minima run over 16 candidates (8
-// with R = 3) before they widen to cost << 16 | (d - dmin). Candidates outside the search
-// range carry bit 15.
+// packed pairs of 16-bit sums finish a window. A candidate's key is cost << 4 | rank in 16
+// bits (cost << 3 with R = 3), two to a word: the digits are of magnitude 2 and 4, so that
+// the sums come out of the products shifted. Packed minima run over 16 candidates (8 with
+// R = 3) before they widen to cost << 16 | (d - dmin). Candidates outside the search range
+// carry bit 15.
 //
-// Bound: vector ALU (packing, 2R adds, key and minimum: 2R + 3 per two candidates; the
-// products themselves take a fifth of that time on the matrix cores). Measured on a
-// 1920 x 1080 pair with 192 candidates, R = 2: 232 us for both views, against 806 us for the
+// Bound: vector ALU (packing, 2R adds, key and minimum: 2R + 3 per two candidates; it issues in
+// 97% of the cycles, the matrix cores are busy in 18%). Measured on a 1920 x 1080 pair with
+// 192 candidates, R = 2: 225 us for both views with their check, against 813 us for the
 // vector-ALU kernel it replaces (two XORs, two popcounts and about six more operations a
-// term); bands of 16 rows measure 2% less there and 3% more on a 960 x 128 region of nine
-// offsets (62 us against 255). Three waves per SIMD at the price of a few spilled registers
-// measure 6% less than two.
+// term); on a 960 x 128 region of nine offsets 78 us against 262. Bands of 16 rows measure 2%
+// less on the first and 3% more on the second; three waves per SIMD at the price of a few
+// spilled registers measure 6% less than two.
 #include <algorithm>
 
 #include "dev_fp4.hpp"
@@ -84,6 +85,10 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
   constexpr int HS = 16 * T - 2 * R;            // candidate columns of a lane half
   constexpr int Z2 = 8 * T;                     // accumulators z and z + Z2 share a packed word
   constexpr int IB = R == 3 ? 3 : 4;            // rank bits of a 16-bit key
+  // the digits' magnitudes: a term adds 2^(IB - 1) times (64 - p . q), so that the sums are
+  // keys already but for the rank
+  constexpr uint32_t kFixed = R == 3 ? kTwo : kFour, kMoving = kTwo;
+  constexpr float kTerms = 64.0f * (1 << (IB - 1)) * NW;
   constexpr int RUN = 1 << IB, NRUN = (Z2 + RUN - 1) / RUN;
   const int n = lane & 31, h = lane >> 5;
   const int W = a.W;
@@ -95,20 +100,20 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
   // those of lane half (m >> 2) & 1 at 4 (m >> 3) + (m & 3)
   const int qm = q0 + ((n >> 2) & 1) * HS + 4 * (n >> 3) + (n & 3);
   const uint32_t foff = 8u * (uint32_t)x + 4u * (uint32_t)h;
-  const uint32_t sign = in_vgpr(kSign);
-  uint32_t moff[T], msign[T], mone[T];
+  const uint32_t sign = in_vgpr(kSign), mag = in_vgpr(kMoving);
+  uint32_t moff[T], msign[T], mmag[T];
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int q = qm + 16 * t;
     moff[t] = q >= 0 && q < W ? 8u * (uint32_t)q + 4u * (uint32_t)h : ~7u;   // ~7: past any row
     const bool in = !MASKED || (q >= 0 && q < W);
     msign[t] = MASKED ? (in ? kSign : 0u) : sign;
-    mone[t] = in ? kOne : 0u;
+    mmag[t] = MASKED ? (in ? kMoving : 0u) : mag;
   }
   // the left view's terms count where the fixed column is inside; a word of the right
   // image outside it is 0
   const bool f_in = RIGHT || (x >= 0 && x < W);
-  const uint32_t fsign = f_in ? kSign : 0u, fone = f_in ? kOne : 0u;
+  const uint32_t fsign = f_in ? kSign : 0u, fmag = f_in ? kFixed : 0u;
   // rank of each candidate within its run (smaller d first), bit 15 where d is outside
   // the range or, right view, the left column is outside the image
   // (accumulators z0 .. z1 hold valid candidates; bits of the others)
@@ -131,15 +136,15 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
       pen[z] = (lo << 15) | (hi << 31) | rank * 0x10001u;
     }
   }
-  // every term adds 64 - p . q = 2 popcount(p ^ q): the windows start at 64 per row, above
-  // 2^23 so that the low bits of the float are the sum
+  // every term adds 64 - p . q = 2 popcount(p ^ q) (times 2^(IB - 1)): the windows start at 64
+  // per row, above 2^23 so that the low bits of the float are the sum
   v16f acc[T];
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int q = q0 + h * HS + 16 * t + r;
-      acc[t][r] = 8388608.0f + (!MASKED || (q >= 0 && q < W) ? 64.0f * NW : 0.0f);
+      acc[t][r] = 8388608.0f + (!MASKED || (q >= 0 && q < W) ? kTerms : 0.0f);
     }
   const uint64_t* fimg = RIGHT ? a.CR : a.CL;
   const uint64_t* mimg = RIGHT ? a.CL : a.CR;
@@ -157,9 +162,9 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
     return w;
   };
   auto add_row = [&](const DenseRow<T>& w, uint32_t flip) {
-    const v4i f = fp4_signs(w.f ^ flip, fsign, fone);
+    const v4i f = fp4_signs(w.f ^ flip, fsign, fmag);
 #pragma unroll
-    for (int t = 0; t < T; ++t) acc[t] = mfma_fp4(fp4_signs(w.m[t], msign[t], mone[t]), f, acc[t]);
+    for (int t = 0; t < T; ++t) acc[t] = mfma_fp4(fp4_signs(w.m[t], msign[t], mmag[t]), f, acc[t]);
   };
   DenseRow<T> enter = load_row(y0 - R), leave = enter;
 #pragma unroll 1
@@ -199,7 +204,7 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
         }
 #pragma unroll
         for (int v = 0; v < 8; ++v)
-          best = __builtin_elementwise_min(best, __builtin_bit_cast(u16x2, (s[v] << (IB - 1)) + pen[z8 + v]));
+          best = __builtin_elementwise_min(best, __builtin_bit_cast(u16x2, s[v] + pen[z8 + v]));
       }
       // widen: cost << 16 | (d - dmin)
       const uint32_t b = __builtin_bit_cast(uint32_t, best);

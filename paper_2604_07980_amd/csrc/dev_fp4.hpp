@@ -27,14 +27,28 @@ __device__ __forceinline__ v4f mfma_fp4(v4i a, v4i b, v4f c) {
 
 // FP4 codes: the sign bit and, repeated eight times, the magnitudes 1, 2 and 4.
 constexpr uint32_t kSign = 0x88888888u, kOne = 0x22222222u, kTwo = 0x44444444u, kFour = 0x66666666u;
-// 32 bits of a word as 32 numbers +-1 (bit 1: -1), seven instructions. sign, one: kSign and
-// kOne, or both 0 for a word whose terms do not count. p . q = 64 - 2 popcount(p ^ q).
-__device__ __forceinline__ v4i fp4_signs(uint32_t w, uint32_t sign, uint32_t one) {
+// (w & sign) | mag and 2 w: v_bitop3_b32 and v_add_u32 issue up to 1.6 times as fast as the
+// and-or and the left shift that the compiler would take (operands in vector registers).
+__device__ __forceinline__ uint32_t and_or(uint32_t w, uint32_t sign, uint32_t mag) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(w), "v"(sign), "v"(mag));
+  return r;
+}
+__device__ __forceinline__ uint32_t twice(uint32_t w) {
+  uint32_t r;
+  asm("v_add_u32 %0, %1, %1" : "=v"(r) : "v"(w));
+  return r;
+}
+// 32 bits of a word as 32 numbers of one magnitude (bit 1: negative), seven instructions. sign,
+// mag: kSign and the magnitude's codes, or both 0 for a word whose terms do not count. With
+// +-1, p . q = 64 - 2 popcount(p ^ q).
+__device__ __forceinline__ v4i fp4_signs(uint32_t w, uint32_t sign, uint32_t mag) {
+  const uint32_t w2 = twice(w), w4 = twice(w2), w8 = twice(w4);
   v4i f;
-  f.x = (int)((w & sign) | one);
-  f.y = (int)(((w << 1) & sign) | one);
-  f.z = (int)(((w << 2) & sign) | one);
-  f.w = (int)(((w << 3) & sign) | one);
+  f.x = (int)and_or(w, sign, mag);
+  f.y = (int)and_or(w2, sign, mag);
+  f.z = (int)and_or(w4, sign, mag);
+  f.w = (int)and_or(w8, sign, mag);
   return f;
 }
 
