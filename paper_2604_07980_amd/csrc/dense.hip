@@ -14,27 +14,32 @@
 // columns at 128 operations each (6 PFLOP/s measured, five times the rate of the vector
 // ALU's two XORs and two popcounts). Sums of +-1 are exact in the fp32 accumulators.
 //
-// One wave per strip of `cols` output columns and band of kBand output rows; it finds the
-// left or the right winners. The strip's columns (32 with the window's halo) are the
-// product's columns, one per lane; the other image's columns are its rows: a lane
-// half holds 16 T consecutive ones in its accumulators, so a chunk of the search is
-// 2 (16 T - 2R) candidate columns. The accumulators hold the vertical window sums: each
-// step adds the products of the entering row and subtracts those of the leaving one (the
-// leaving row's signs flipped). The horizontal window runs along a diagonal: the neighbour
-// column in the next lane pairs with the next accumulator, so 2R wave-wide DPP adds of
-// packed pairs of 16-bit sums finish a window. A candidate's key is cost << 4 | rank in 16
-// bits (cost << 3 with R = 3), two to a word: the digits are of magnitude 2 and 4, so that
-// the sums come out of the products shifted. Packed minima run over 16 candidates (8 with
-// R = 3) before they widen to cost << 16 | (d - dmin). Candidates outside the search range
-// carry bit 15.
+// One wave per strip of `cols` output columns of the left view and band of kBand output rows.
+// The strip's columns (32 with the window's halo) are the product's columns, one per lane; the
+// right image's columns are its rows: a lane half holds 16 T consecutive ones in its
+// accumulators, so a chunk of the search is 2 (16 T - 2R) candidate columns. The accumulators
+// hold the vertical window sums: each step adds the products of the entering row and
+// subtracts those of the leaving one (the leaving row's signs flipped). The horizontal window
+// runs along a diagonal: the neighbour column in the next lane pairs with the next
+// accumulator, so 2R wave-wide DPP adds of packed pairs of 16-bit sums finish a window. A
+// candidate's key is cost << 4 | rank in 16 bits (cost << 3 with R = 3), two to a word: the
+// digits are of magnitude 2 and 4, so that the sums come out of the products shifted. Packed
+// minima run over 16 candidates (8 with R = 3) before they widen to cost << 16 | (d - dmin).
+// Candidates outside the search range carry bit 15.
 //
-// Bound: vector ALU (packing, 2R adds, key and minimum: 2R + 3 per two candidates; it issues in
-// 97% of the cycles, the matrix cores are busy in 18%). Measured on a 1920 x 1080 pair with
-// 192 candidates, R = 2: 225 us for both views with their check, against 813 us for the
-// vector-ALU kernel it replaces (two XORs, two popcounts and about six more operations a
-// term); on a 960 x 128 region of nine offsets 78 us against 262. Bands of 16 rows measure 2%
-// less on the first and 3% more on the second; three waves per SIMD at the price of a few
-// spilled registers measure 6% less than two.
+// The same costs give the right winners: those of a right column lie in one accumulator of
+// every lane, so the keys (with the lane's rank in place of the accumulator's) turn through
+// LDS, a lane takes a right column's 32, and the least goes to the column's word in memory by
+// an atomic minimum, where the strips that see the column meet.
+//
+// Bound: vector ALU (packing, 2R adds, left and right key and minimum: 2R + 5 per two
+// candidates; it issues in 82% of the cycles, the matrix cores are busy in 12%). Measured on a
+// 1920 x 1080 pair with 192 candidates, R = 2: 175 us with the check, against 225 with a pass
+// of its own for the right winners and 813 for the vector ALU alone (two XORs, two popcounts
+// and about six more operations a term); on a 960 x 128 region of nine offsets 67 us against
+// 78 and 262. Bands of 10 rows measure 1.5% less on the first and 2% more on the second, of 6
+// rows 2% and 10% more; three waves per SIMD at the price of 25 spilled registers measure 10%
+// less than two; the atomics cost 2%.
 #include <algorithm>
 
 #include "dev_fp4.hpp"
@@ -51,12 +56,16 @@ struct DenseArgs {
   int32_t dlo, nd;            // disparities dlo .. dlo + nd - 1
   int32_t d_out;              // dmin, which the winners' indices are added to (dlo is at most
                               // W + 512: from W on every candidate's word lies outside)
-  int16_t* out;               // [H][W] winning disparity (-1: no candidate)
+  int16_t* left;              // [H][W] left winners' disparity (-1: no candidate)
+  uint32_t* right;            // [H][W] right winners' cost << 16 | (d - dlo), kNoKey at first
   // several pairs in one launch (grid z): pair z reads CL + z * cl_zstride (words; the
-  // right image is shared) and writes out + z * out_zstride
+  // right image is shared) and writes left and right + z * out_zstride
   int64_t cl_zstride, out_zstride;
   int32_t cols, chunks;       // output columns per wave, chunks of the search
+  int32_t strips, bands;      // of a pair
 };
+
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
 
 using namespace dev;
 
@@ -73,18 +82,29 @@ struct DenseRow {
   uint32_t f, m[T];
 };
 
-// RIGHT = 0: the left view (fixed column x of CL, moving columns x - d of CR);
-// RIGHT = 1: the right view (fixed column x of CR, moving columns x + d of CL).
-// MASKED (right view only): some moving column of the chunk lies outside the image, where
-// no term counts.
-template <int R, int RIGHT, int T, bool MASKED>
+// How the right winners' keys change lanes: row h Z2 + z of LDS holds accumulator z of lane
+// half h (packed with z + Z2) for the strip's 32 columns; 36 words a row, so that 16-byte
+// reads of 16 rows hit all banks.
+template <int T>
+struct DenseTurn {
+  static constexpr int Z2 = 8 * T, ROWS = 2 * Z2, STRIDE = 36;
+  static constexpr int WORDS = ROWS * STRIDE;
+};
+
+template <int R>
+constexpr int rank_bits() { return R == 3 ? 3 : 4; }
+// every key of a valid candidate is below this, every other one above
+template <int R>
+constexpr uint32_t none_from() { return (0x8000u << (16 - rank_bits<R>())) - 0x10000u; }
+
+template <int R, int T>
 __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, int chunk, int lane,
-                                            uint32_t* __restrict__ keys) {
+                                            uint32_t* __restrict__ keys, uint32_t* __restrict__ turn) {
   constexpr int NW = 2 * R + 1;                 // window rows and columns
   constexpr int NR = kBand + 2 * R;             // rows walked
   constexpr int HS = 16 * T - 2 * R;            // candidate columns of a lane half
   constexpr int Z2 = 8 * T;                     // accumulators z and z + Z2 share a packed word
-  constexpr int IB = R == 3 ? 3 : 4;            // rank bits of a 16-bit key
+  constexpr int IB = rank_bits<R>();            // rank bits of a 16-bit key
   // the digits' magnitudes: a term adds 2^(IB - 1) times (64 - p . q), so that the sums are
   // keys already but for the rank
   constexpr uint32_t kFixed = R == 3 ? kTwo : kFour, kMoving = kTwo;
@@ -95,34 +115,31 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
   const int x = xs + n - R;                     // the lane's fixed column
   const int c = xs + n - 2 * R;                 // centre of the window that ends in lane n
   // accumulator z of lane half h is moving column q0 + h HS + z (a window's last column)
-  const int q0 = (RIGHT ? xs + a.dlo : xs - (a.dlo + a.nd - 1)) + 2 * HS * chunk - R;
+  const int q0 = xs - (a.dlo + a.nd - 1) + 2 * HS * chunk - R;
   // loads: lane l gives row l & 31 of a product's first operand, whose accumulators are
   // those of lane half (m >> 2) & 1 at 4 (m >> 3) + (m & 3)
   const int qm = q0 + ((n >> 2) & 1) * HS + 4 * (n >> 3) + (n & 3);
   const uint32_t foff = 8u * (uint32_t)x + 4u * (uint32_t)h;
   const uint32_t sign = in_vgpr(kSign), mag = in_vgpr(kMoving);
-  uint32_t moff[T], msign[T], mmag[T];
+  uint32_t moff[T];
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int q = qm + 16 * t;
     moff[t] = q >= 0 && q < W ? 8u * (uint32_t)q + 4u * (uint32_t)h : ~7u;   // ~7: past any row
-    const bool in = !MASKED || (q >= 0 && q < W);
-    msign[t] = MASKED ? (in ? kSign : 0u) : sign;
-    mmag[t] = MASKED ? (in ? kMoving : 0u) : mag;
   }
-  // the left view's terms count where the fixed column is inside; a word of the right
-  // image outside it is 0
-  const bool f_in = RIGHT || (x >= 0 && x < W);
+  // terms count where the left column is inside; a word of the right image outside it is 0
+  const bool f_in = x >= 0 && x < W;
   const uint32_t fsign = f_in ? kSign : 0u, fmag = f_in ? kFixed : 0u;
   // rank of each candidate within its run (smaller d first), bit 15 where d is outside
-  // the range or, right view, the left column is outside the image
+  // the range or the lane's window is not one of the strip's output columns
   // (accumulators z0 .. z1 hold valid candidates; bits of the others)
   uint32_t pen[Z2];
   {
     const int qc0 = q0 + h * HS - R;            // accumulator 0's centre
-    const int k0 = RIGHT ? c + a.dlo - qc0 : c - a.dlo - (a.nd - 1) - qc0;   // first candidate
+    const int k0 = c - a.dlo - (a.nd - 1) - qc0;   // first candidate
+    const bool c_out = n >= 2 * R && n < 2 * R + a.cols && c < W;
     const int z0 = max(k0, 2 * R);
-    const int z1 = RIGHT ? min(k0 + a.nd - 1, W - 1 - qc0) : k0 + a.nd - 1;
+    const int z1 = c_out ? k0 + a.nd - 1 : -1;
     auto bits_from = [](int z) {                // bits z and up of 32
       return z >= 32 ? 0u : z <= 0 ? 0xFFFFFFFFu : 0xFFFFFFFFu << z;
     };
@@ -131,7 +148,7 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
     for (int k = 0; k < T / 2 + 1; ++k) bad[k] = ~(bits_from(z0 - 32 * k) & ~bits_from(z1 + 1 - 32 * k));
 #pragma unroll
     for (int z = 0; z < Z2; ++z) {
-      const uint32_t rank = (uint32_t)(RIGHT ? z % RUN : RUN - 1 - z % RUN);
+      const uint32_t rank = (uint32_t)(RUN - 1 - z % RUN);
       const uint32_t lo = (bad[z / 32] >> (z % 32)) & 1u, hi = (bad[(z + Z2) / 32] >> ((z + Z2) % 32)) & 1u;
       pen[z] = (lo << 15) | (hi << 31) | rank * 0x10001u;
     }
@@ -142,19 +159,14 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int q = q0 + h * HS + 16 * t + r;
-      acc[t][r] = 8388608.0f + (!MASKED || (q >= 0 && q < W) ? kTerms : 0.0f);
-    }
-  const uint64_t* fimg = RIGHT ? a.CR : a.CL;
-  const uint64_t* mimg = RIGHT ? a.CL : a.CR;
+    for (int r = 0; r < 16; ++r) acc[t][r] = 8388608.0f + (f_in ? kTerms : 0.0f);
   // rows outside the image read as 0 in both views (no difference), columns outside it as 0
   auto load_row = [&](int y) {
     const bool in = y >= 0 && y < a.H;
     const size_t ro = (size_t)(in ? y : 0) * (size_t)a.pitch;
     const int nrec = in ? W * 8 : 0;
-    const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc((void*)(fimg + ro), (short)0, nrec, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc((void*)(mimg + ro), (short)0, nrec, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc((void*)(a.CL + ro), (short)0, nrec, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc((void*)(a.CR + ro), (short)0, nrec, 0x00020000);
     DenseRow<T> w;
     w.f = __builtin_amdgcn_raw_buffer_load_b32(rf, foff, 0, 0);
 #pragma unroll
@@ -164,8 +176,11 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
   auto add_row = [&](const DenseRow<T>& w, uint32_t flip) {
     const v4i f = fp4_signs(w.f ^ flip, fsign, fmag);
 #pragma unroll
-    for (int t = 0; t < T; ++t) acc[t] = mfma_fp4(fp4_signs(w.m[t], msign[t], mmag[t]), f, acc[t]);
+    for (int t = 0; t < T; ++t) acc[t] = mfma_fp4(fp4_signs(w.m[t], sign, mag), f, acc[t]);
   };
+  const uint32_t cost_bits = in_vgpr(0x10001u * (0xFFFFu & ~(uint32_t)(RUN - 1)));
+  const uint32_t lane_rank = 0x10001u * (uint32_t)(n & (RUN - 1));
+  uint32_t* __restrict__ put = turn + h * Z2 * DenseTurn<T>::STRIDE + n;
   DenseRow<T> enter = load_row(y0 - R), leave = enter;
 #pragma unroll 1
   for (int i = 0; i < NR; ++i) {
@@ -203,8 +218,13 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int v = 0; v < 8; ++v)
-          best = __builtin_elementwise_min(best, __builtin_bit_cast(u16x2, s[v] + pen[z8 + v]));
+        for (int v = 0; v < 8; ++v) {
+          const uint32_t k = s[v] + pen[z8 + v];
+          best = __builtin_elementwise_min(best, __builtin_bit_cast(u16x2, k));
+          // the right winner of a column is the least over lanes, the same rank for all: the
+          // lane's rank in its place (smaller d first)
+          put[(z8 + v) * DenseTurn<T>::STRIDE] = and_or(k, cost_bits, lane_rank);
+        }
       }
       // widen: cost << 16 | (d - dmin)
       const uint32_t b = __builtin_bit_cast(uint32_t, best);
@@ -212,81 +232,119 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
       for (int hw = 0; hw < 2; ++hw) {
         const uint32_t v = hw ? b >> 16 : b & 0xFFFFu;
         const int q = q0 + h * HS + hw * Z2 + u * RUN - R;
-        const int base = (RIGHT ? q - c : c - q - (RUN - 1)) - a.dlo;
+        const int base = c - q - (RUN - 1) - a.dlo;
         const uint32_t wide = ((v & ~(uint32_t)(RUN - 1)) << (16 - IB)) + (v & (RUN - 1)) + (uint32_t)base;
         key = min(key, wide);
       }
     }
     uint32_t* kp = keys + (i - 2 * R) * 64 + lane;
     *kp = chunk == 0 ? key : min(*kp, key);
+    // right winners: a lane takes a row of the turned keys, RUN columns at a time
+    wave_sync();
+    const int y = y0 + i - 2 * R;
+#pragma unroll
+    for (int p = 0; p < (DenseTurn<T>::ROWS + 63) / 64; ++p) {
+      const int row = min(lane + 64 * p, DenseTurn<T>::ROWS - 1);
+      const bool row_in = DenseTurn<T>::ROWS % 64 == 0 || lane + 64 * p < DenseTurn<T>::ROWS;
+      const uint4* __restrict__ in = (const uint4*)(turn + row * DenseTurn<T>::STRIDE);
+      u16x2 m[32 / RUN];
+#pragma unroll
+      for (int g = 0; g < 32 / RUN; ++g) {
+        m[g] = u16x2{0xFFFF, 0xFFFF};
+#pragma unroll
+        for (int j = 0; j < RUN / 4; ++j) {
+          const uint4 v = in[g * (RUN / 4) + j];
+          m[g] = __builtin_elementwise_min(m[g], __builtin_bit_cast(u16x2, v.x));
+          m[g] = __builtin_elementwise_min(m[g], __builtin_bit_cast(u16x2, v.y));
+          m[g] = __builtin_elementwise_min(m[g], __builtin_bit_cast(u16x2, v.z));
+          m[g] = __builtin_elementwise_min(m[g], __builtin_bit_cast(u16x2, v.w));
+        }
+      }
+      const int hr = row >= Z2 ? 1 : 0, z = row - hr * Z2;
+#pragma unroll
+      for (int hw = 0; hw < 2; ++hw) {
+        const int q = q0 + hr * HS + hw * Z2 + z - R;
+        uint32_t rkey = kNoKey;
+#pragma unroll
+        for (int g = 0; g < 32 / RUN; ++g) {
+          const uint32_t b = __builtin_bit_cast(uint32_t, m[g]);
+          const uint32_t v = hw ? b >> 16 : b & 0xFFFFu;
+          const int base = xs + RUN * g - 2 * R - q - a.dlo;
+          rkey = min(rkey, ((v & ~(uint32_t)(RUN - 1)) << (16 - IB)) + (v & (RUN - 1)) + (uint32_t)base);
+        }
+        if (row_in && rkey < none_from<R>() && q >= 0 && q < W && y < a.H)
+          __hip_atomic_fetch_min(a.right + ((size_t)y * W + q), rkey, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    wave_sync();
   }
 }
 
-template <int R, int RIGHT, int T>
-__device__ __forceinline__ void dense_strip(const DenseArgs& a, int xs, int y0, int lane,
-                                            uint32_t* __restrict__ keys) {
-  constexpr int HS = 16 * T - 2 * R;
+// grid x: waves over the pair's strips and bands, z: pairs
+template <int R, int T>
+__global__ __launch_bounds__(256, T > 4 ? 2 : 3) void dense_kernel(DenseArgs a) {
+  __shared__ uint32_t keys[4 * kBand * 64];
+  __shared__ __attribute__((aligned(16))) uint32_t turn[4 * DenseTurn<T>::WORDS];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int item = (int)blockIdx.x * 4 + wave;
+  const int band = item / a.strips;
+  if (band >= a.bands) return;             // whole wave; the kernel has no barrier
+  const int y0 = band * kBand, xs = (item % a.strips) * a.cols;
+  a.CL += (int64_t)blockIdx.z * a.cl_zstride;
+  a.left += (int64_t)blockIdx.z * a.out_zstride;
+  a.right += (int64_t)blockIdx.z * a.out_zstride;
+  uint32_t* kw = keys + wave * kBand * 64;
 #pragma unroll 1
-  for (int j = 0; j < a.chunks; ++j) {
-    const int q0 = xs + a.dlo + 2 * HS * j - R;
-    if (RIGHT && (q0 < 0 || q0 + 2 * HS + 2 * R > a.W)) dense_chunk<R, RIGHT, T, true>(a, xs, y0, j, lane, keys);
-    else dense_chunk<R, RIGHT, T, false>(a, xs, y0, j, lane, keys);
-  }
+  for (int j = 0; j < a.chunks; ++j)
+    dense_chunk<R, T>(a, xs, y0, j, lane, kw, turn + wave * DenseTurn<T>::WORDS);
   const int n = lane & 31, c = xs + n - 2 * R;
-  // every key of a valid candidate is below this, every other one above
-  constexpr uint32_t kNone = (0x8000u << (R == 3 ? 13 : 12)) - 0x10000u;
 #pragma unroll
   for (int o = 0; o < kBand; ++o) {
     // the two lane halves hold different candidates of the same column
-    uint32_t key = keys[o * 64 + lane];
+    uint32_t key = kw[o * 64 + lane];
     key = min(key, (uint32_t)__shfl_xor((int)key, 32, 64));
     const int y = y0 + o;
     if (lane >= 2 * R && lane < 2 * R + a.cols && c < a.W && y < a.H)
-      a.out[(size_t)y * a.W + c] = key >= kNone ? (int16_t)-1 : (int16_t)(a.d_out + (int)(key & 0xFFFFu));
+      a.left[(size_t)y * a.W + c] = key >= none_from<R>() ? (int16_t)-1 : (int16_t)(a.d_out + (int)(key & 0xFFFFu));
   }
 }
 
-// grid z: pairs of the left view, then the same pairs of the right view
-template <int R, int T>
-__global__ __launch_bounds__(256, T > 4 ? 2 : 3) void dense_kernel(DenseArgs a, int16_t* out_right, int nz) {
-  __shared__ uint32_t keys[4 * kBand * 64];
-  const bool right = (int)blockIdx.z >= nz;
-  const int z = (int)blockIdx.z - (right ? nz : 0);
-  a.CL += (int64_t)z * a.cl_zstride;
-  a.out = (right ? out_right : a.out) + (int64_t)z * a.out_zstride;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int y0 = ((int)blockIdx.y * 4 + wave) * kBand;
-  if (y0 >= a.H) return;                   // whole wave; the kernel has no barrier
-  const int xs = (int)blockIdx.x * a.cols;
-  uint32_t* kw = keys + wave * kBand * 64;
-  if (right) dense_strip<R, 1, T>(a, xs, y0, lane, kw);
-  else dense_strip<R, 0, T>(a, xs, y0, lane, kw);
+__global__ __launch_bounds__(256) void dense_clear_kernel(uint32_t* p, size_t n) {
+  const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
+  if (i + 4 <= n) *(uint4*)(p + i) = uint4{kNoKey, kNoKey, kNoKey, kNoKey};
+  else
+    for (size_t k = i; k < n; ++k) p[k] = kNoKey;
 }
 
-// The L/R check of one row segment of 256 pixels. With `partial` set, the workgroup also
-// stores how many of its checked disparities are > d_min at
+// The L/R check of one row segment of 256 pixels; disp holds the left winners and receives
+// the checked ones. With `right_out` set it receives the right winners' disparities. With
+// `partial` set, the workgroup also stores how many of its checked disparities are > d_min at
 // partial[(z * H + y) * gridDim.x + blockIdx.x].
-__global__ __launch_bounds__(256) void dense_check_kernel(const int16_t* __restrict__ dl,
-                                                          const int16_t* __restrict__ dr, int W,
-                                                          int H, int lr_tol, int16_t* disp,
-                                                          int d_min, int32_t* partial) {
+__global__ __launch_bounds__(256) void dense_check_kernel(const uint32_t* __restrict__ right, int W, int H,
+                                                          int d_out, int lr_tol, int16_t* disp,
+                                                          int16_t* __restrict__ right_out, int d_min,
+                                                          int32_t* partial) {
   __shared__ int part[4];
   const size_t plane = (size_t)blockIdx.z * W * H;   // pair z of a multi-pair launch
-  dl += plane;
-  dr += plane;
+  right += plane;
   disp += plane;
   const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
+  auto right_disp = [&](int xr) {
+    const uint32_t key = right[(size_t)y * W + xr];
+    return key == kNoKey ? -1 : (int)(int16_t)(d_out + (int)(key & 0xFFFFu));
+  };
   int above = 0;
   if (x < W) {
-    const int d = dl[(size_t)y * W + x];
+    const int d = disp[(size_t)y * W + x];
     const int xr = x - d;
     int ok = 0;
     if (d >= 0 && xr >= 0) {
-      const int db = dr[(size_t)y * W + xr];
+      const int db = right_disp(xr);
       ok = db >= 0 && abs(d - db) <= lr_tol;
     }
     disp[(size_t)y * W + x] = ok ? (int16_t)d : (int16_t)-1;
+    if (right_out) right_out[plane + (size_t)y * W + x] = (int16_t)right_disp(x);
     above = ok && d > d_min ? 1 : 0;
   }
   if (!partial) return;   // uniform over the launch
@@ -310,19 +368,21 @@ __global__ __launch_bounds__(256) void count_above_kernel(const int32_t* __restr
   if (threadIdx.x == 0) counts[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-// Both views of nz pairs in one launch. A wave covers chunks x 2 (16 T - 2R) candidate
-// columns for at most 32 - 2R output columns; the shape (T, chunks, columns) with the least
-// work per output column is taken (a chunk's work: T products and reductions and about
-// 0.8 of one for the fixed column and the row's overhead).
+// Both views' winners of nz pairs in one launch. A wave covers chunks x 2 (16 T - 2R)
+// candidate columns for at most 32 - 2R output columns; the shape (T, chunks, columns) with
+// the least work per output column is taken (a chunk's work: T products and reductions and
+// about 0.9 of one for the fixed column, the right winners and the row's overhead, fitted to
+// T = 3, 4 and 5 each alone at 48 to 256 candidates, where the shape taken is within 3% of the
+// best of them).
 template <int R>
-hipError_t launch_dense_r(DenseArgs a, int16_t* out_right, hipStream_t s, int nz) {
+hipError_t launch_dense_r(DenseArgs a, hipStream_t s, int nz) {
   int best_t = 0;
   double best = 0;
   for (int t = 3; t <= 5; ++t) {
     const int per = 2 * (16 * t - 2 * R);
     for (int n = (a.nd + 7 + per - 1) / per; n <= (a.nd + 31) / per + 1; ++n) {
       const int cols = std::min(32 - 2 * R, n * per - a.nd + 1);
-      const double work = n * (t + 0.8) / cols;
+      const double work = n * (t + 0.9) / cols;
       if (cols >= 8 && (best_t == 0 || work < best)) {
         best = work;
         best_t = t;
@@ -331,11 +391,22 @@ hipError_t launch_dense_r(DenseArgs a, int16_t* out_right, hipStream_t s, int nz
       }
     }
   }
-  const dim3 grid((a.W + a.cols - 1) / a.cols, (a.H + 4 * kBand - 1) / (4 * kBand), 2 * nz);
-  if (best_t == 3) dense_kernel<R, 3><<<grid, 256, 0, s>>>(a, out_right, nz);
-  else if (best_t == 4) dense_kernel<R, 4><<<grid, 256, 0, s>>>(a, out_right, nz);
-  else dense_kernel<R, 5><<<grid, 256, 0, s>>>(a, out_right, nz);
+  const size_t words = (size_t)nz * a.W * a.H;
+  dense_clear_kernel<<<(unsigned)((words + 1023) / 1024), 256, 0, s>>>(a.right, words);
+  a.strips = (a.W + a.cols - 1) / a.cols;
+  a.bands = (a.H + kBand - 1) / kBand;
+  const dim3 grid((a.strips * a.bands + 3) / 4, 1, nz);
+  if (best_t == 3) dense_kernel<R, 3><<<grid, 256, 0, s>>>(a);
+  else if (best_t == 4) dense_kernel<R, 4><<<grid, 256, 0, s>>>(a);
+  else dense_kernel<R, 5><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
+}
+
+hipError_t launch_dense_any(const DenseArgs& a, int radius, hipStream_t s, int nz) {
+  if (radius == 1) return launch_dense_r<1>(a, s, nz);
+  if (radius == 2) return launch_dense_r<2>(a, s, nz);
+  if (radius == 3) return launch_dense_r<3>(a, s, nz);
+  return hipErrorNotSupported;
 }
 
 }  // namespace
@@ -343,19 +414,17 @@ hipError_t launch_dense_r(DenseArgs a, int16_t* out_right, hipStream_t s, int nz
 bool dense_radius_supported(int radius) { return radius >= 1 && radius <= 3; }
 
 hipError_t launch_dense(const uint64_t* CL, const uint64_t* CR, int W, int H, int pitch, int dmin,
-                        int dmax, int radius, int lr_tol, int16_t* disp, int16_t* d_left,
-                        int16_t* d_right, hipStream_t stream, const LaunchTimer* timer) {
-  const DenseArgs args = {CL, CR, W, H, pitch, std::min(dmin, W + 512), dmax - dmin + 1, dmin, d_left, 0, 0, 0, 0};
+                        int dmax, int radius, int lr_tol, int16_t* disp, uint32_t* right,
+                        int16_t* disp_right, hipStream_t stream, const LaunchTimer* timer) {
+  const DenseArgs args = {CL, CR, W, H, pitch, std::min(dmin, W + 512), dmax - dmin + 1, dmin, disp, right,
+                          0, 0, 0, 0, 0, 0};
   if (timer) timer->before(timer->ctx, "dense", stream);
-  hipError_t e = hipErrorNotSupported;
-  if (radius == 1) e = launch_dense_r<1>(args, d_right, stream, 1);
-  if (radius == 2) e = launch_dense_r<2>(args, d_right, stream, 1);
-  if (radius == 3) e = launch_dense_r<3>(args, d_right, stream, 1);
+  const hipError_t e = launch_dense_any(args, radius, stream, 1);
   if (timer) timer->after(timer->ctx, "dense", stream);
   if (e != hipSuccess) return e;
   if (timer) timer->before(timer->ctx, "dense_check", stream);
-  dense_check_kernel<<<dim3((W + 255) / 256, H), 256, 0, stream>>>(d_left, d_right, W, H, lr_tol,
-                                                                   disp, 0, nullptr);
+  dense_check_kernel<<<dim3((W + 255) / 256, H), 256, 0, stream>>>(right, W, H, dmin, lr_tol, disp,
+                                                                   disp_right, 0, nullptr);
   if (timer) timer->after(timer->ctx, "dense_check", stream);
   return hipGetLastError();
 }
@@ -364,21 +433,17 @@ hipError_t launch_dense(const uint64_t* CL, const uint64_t* CR, int W, int H, in
 // descriptors moved down by z more rows; then the pixels above d_min of each map.
 hipError_t launch_dense_offsets(const uint64_t* CL0, const uint64_t* CR, int W, int H, int pitch,
                                 int nz, int dmin, int dmax, int radius, int lr_tol, int d_min,
-                                int16_t* disp, int16_t* d_left, int16_t* d_right, int32_t* partial,
-                                int32_t* counts, hipStream_t stream, const LaunchTimer* timer) {
-  const int64_t plane = (int64_t)W * H;
-  const DenseArgs args = {CL0, CR, W, H, pitch, std::min(dmin, W + 512), dmax - dmin + 1, dmin, d_left, -(int64_t)pitch,
-                          plane, 0, 0};
+                                int16_t* disp, uint32_t* right, int32_t* partial, int32_t* counts,
+                                hipStream_t stream, const LaunchTimer* timer) {
+  const DenseArgs args = {CL0, CR, W, H, pitch, std::min(dmin, W + 512), dmax - dmin + 1, dmin, disp, right,
+                          -(int64_t)pitch, (int64_t)W * H, 0, 0, 0, 0};
   if (timer) timer->before(timer->ctx, "rect_dense", stream);
-  hipError_t e = hipErrorNotSupported;
-  if (radius == 1) e = launch_dense_r<1>(args, d_right, stream, nz);
-  if (radius == 2) e = launch_dense_r<2>(args, d_right, stream, nz);
-  if (radius == 3) e = launch_dense_r<3>(args, d_right, stream, nz);
+  const hipError_t e = launch_dense_any(args, radius, stream, nz);
   if (timer) timer->after(timer->ctx, "rect_dense", stream);
   if (e != hipSuccess) return e;
   if (timer) timer->before(timer->ctx, "rect_count", stream);
   const int bx = (W + 255) / 256;
-  dense_check_kernel<<<dim3(bx, H, nz), 256, 0, stream>>>(d_left, d_right, W, H, lr_tol, disp, d_min,
+  dense_check_kernel<<<dim3(bx, H, nz), 256, 0, stream>>>(right, W, H, dmin, lr_tol, disp, nullptr, d_min,
                                                           partial);
   count_above_kernel<<<nz, 256, 0, stream>>>(partial, H * bx, counts);
   if (timer) timer->after(timer->ctx, "rect_count", stream);
