@@ -481,8 +481,9 @@ int32_t ocsr_rect_filter_update(ocsr_rect_filter* f, const int32_t* counts, int3
  * launch (1..64, default 16). The launch deals its work items over this grid. */
 #define OCSR_OPTION_MATCH_WGS_PER_CU 4
 /* OCSR_OPTION_BLOCKS_PER_WAVE: blocks each wave of a matching workgroup takes per work
- * item (1..8, default 1); a work item holds 4 x this many blocks of one box. A variant whose
- * waves take several adjacent blocks together (rows = 1 or 2 below) counts those as one. */
+ * item (1..8; until it is set 1, 2 or 3 by the call's boxes and image sizes); a work item
+ * holds 4 x this many blocks of one box. A variant whose waves take several adjacent blocks
+ * together (rows = 1 or 2 below) counts those as one. */
 #define OCSR_OPTION_BLOCKS_PER_WAVE 5
 /* OCSR_OPTION_GRAPH: 1 submits whole-frame and batch calls (ocsr_range_frame,
  * ocsr_range_batch) as HIP graphs: the first call with a given set of arguments
@@ -507,8 +508,8 @@ int32_t ocsr_rect_filter_update(ocsr_rect_filter* f, const int32_t* counts, int3
  * its tile or leaves. Results and the tiles made are the same either way. */
 #define OCSR_OPTION_CENSUS_TILE_LIST 7
 /* OCSR_OPTION_LEVEL_LAUNCHES: how the blocks of the two levels are matched. 0 (default):
- * one launch for both levels in calls of one frame when a kernel for the pair of chosen
- * variants is built, one launch per level otherwise; 1: always one launch per level;
+ * one launch for both levels in calls of one frame, and of batches except the largest, when
+ * a kernel for the pair of chosen variants is built, one launch per level otherwise; 1: always one launch per level;
  * 2: one launch for both levels whenever such a kernel is built. Results are identical
  * either way. */
 #define OCSR_OPTION_LEVEL_LAUNCHES 8

@@ -45,7 +45,7 @@ struct ocsr_ctx {
   // matching kernel variants chosen for (bw, bh, level candidates), e.g. by a tuner
   std::map<std::array<int, 3>, std::array<int, 3>> variants;
   int match_wgs_per_cu = 16;
-  int blocks_per_wave = 1;
+  int blocks_per_wave = 0;   // 0: by the call's size (deal_items)
   int full_census = 0;
   int census_list = 1;
   int level_launches = 0;   // OCSR_OPTION_LEVEL_LAUNCHES
@@ -339,12 +339,26 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
   d->cap_blocks = cap_blocks;
   // a wave of the matrix-core kernels takes four (rows = 1) or two (rows = 2) adjacent blocks
   // together, of the others one
-  for (int l = 0; l < 2; ++l) {
-    d->group_x[l] = d->path[l].rows == 1 ? 4 : d->path[l].rows == 2 ? 2 : 1;
-    d->item_blocks[l] = kItemWaves * (d->group_x[l] == 4 ? 1 : ctx->blocks_per_wave);
-  }
+  for (int l = 0; l < 2; ++l) d->group_x[l] = d->path[l].rows == 1 ? 4 : d->path[l].rows == 2 ? 2 : 1;
   d->full_census = ctx->full_census;
   return OCSR_OK;
+}
+
+// The size of the matching work items, unless the caller set it. An item's box, its geometry
+// and its occluders are looked up per item, which larger items share out and which smaller
+// ones hide by their number. The number of blocks is known on the device only; match_work
+// stands in for it. Measured, one wave taking 1 / 2 / 3 groups, us per call:
+//   133 M (1080p, 64 boxes)  27.5 / 29.9 / -      249 M (1080p, 120)     35.2 / 34.5 / 36.4
+//   364 M (4 x 1200p)        49.0 / 47.6 / 50.8   730 M (8 x 1200p)      79.7 / 74.0 / 75.0
+//   933 M (4 x 1200p, 400)   83.7 / 76.6 / 74.2  1405 M (16 x 1200p)    130.5 / 121.6 / 115.9
+//  1659 M (2160p, 200)       98.2 / 91.0 / 91.6  2507 M (16 x 1200p)    205.3 / 181.1 / 174.3
+// A vertical range multiplies a group's own work: 124 M 42.5 / 55.0 / 72.1, 498 M 93.7 / 97.5 /
+// 109.0, 1327 M 151.1 / 138.0 / 143.3.
+void deal_items(const ocsr_ctx* ctx, const FramesDev& FR, bool fused, MatchParamsDev* d) {
+  const double work = match_work(FR);
+  const int by_size = fused ? 1 : d->vertical ? (work < 900e6 ? 1 : 2) : work < 240e6 ? 1 : work < 900e6 ? 2 : 3;
+  const int n = ctx->blocks_per_wave > 0 ? ctx->blocks_per_wave : by_size;
+  for (int l = 0; l < 2; ++l) d->item_blocks[l] = kItemWaves * (d->group_x[l] == 4 ? 1 : n);
 }
 
 DebugDev make_debug(const ocsr_debug* dbg) {
@@ -466,6 +480,7 @@ int32_t range_frames(ocsr_ctx* ctx, const ocsr_frame* frames, int n_frames,
   }
   MatchWs mws = match_ws_carve(base, n_frames, n_total, cap_blocks);
   const bool fused = ctx->use_fused && fused_available(P, FR, fp->sx, fp->sy);
+  deal_items(ctx, FR, fused, &P);
   const int sentinel = fp->sentinel ? 1 : 0;
   // the whole launch sequence of the call, on stream s
   auto enqueue = [&](hipStream_t s, const LaunchTimer* tp) -> int32_t {
@@ -557,6 +572,7 @@ int32_t match_boxes_impl(ocsr_ctx* ctx, const ocsr_level* lv0, const ocsr_level*
   FR.f[0].H = lv0->height;
   FR.f[0].box_off = 0;
   FR.f[0].n_boxes = n_boxes;
+  deal_items(ctx, FR, false, &P);
   MatchWs mws = match_ws_carve(ws, 1, n_boxes, cap_blocks);
   LaunchTimer t = make_timer(ctx);
   hipError_t e = launch_match(P, FR, boxes, mws, out, make_debug(dbg), false,

@@ -415,6 +415,12 @@ hipError_t launch_plan_and_census(const MatchParamsDev& P, const FramesDev& FR,
                       P, FR, boxes, ws, sx, sy, sentinel);
 }
 
+double match_work(const FramesDev& FR) {
+  double work = 0;
+  for (int f = 0; f < FR.n; ++f) work += (double)FR.f[f].n_boxes * FR.f[f].W * FR.f[f].H;
+  return work;
+}
+
 hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr_box* boxes,
                         const MatchWs& ws, ocsr_box_result* out, const DebugDev& dbg,
                         bool plan_done, int n_match_wgs, int level_launches, hipStream_t stream,
@@ -431,12 +437,16 @@ hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr
     e = launch_match_vertical(P, FR, ws, dbg, n_match_wgs, stream, timer);
     if (e != hipSuccess) return e;
   } else if (!dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd &&
-             (level_launches == 2 || (level_launches == 0 && FR.n == 1)) &&
+             (level_launches == 2 ||
+              (level_launches == 0 &&
+               (FR.n == 1 || match_work(FR) < (P.item_blocks[1] > kItemWaves ? 2000e6 : 700e6)))) &&
              launch_pair(P, FR, ws, n_match_wgs, stream, nullptr, false)) {
-    // one launch for both levels: in a one-frame call the far level alone cannot fill
-    // the GPU, and its blocks fill the close level's tail (whole 1080p frame: 31 against
-    // 38 us per frame); each level of a batch fills the GPU by itself, and there the two
-    // forms are about even (16 frames: 117.5 against 10.3 + 109.2 us)
+    // one launch for both levels: the far level alone cannot fill the GPU, and its blocks
+    // fill the close level's tail. Whole calls, one launch against two: 1080p frame 24.9 and
+    // 30.6 us, 3 x 717p 23.5 and 29.0, 8 x 1200p 74.0 and 77.7, 16 x 1200p 115.9 and 118.2.
+    // The kernel of both levels has more registers to spill, and past a batch of that size
+    // one launch per level is the faster: 16 x 1200p of 1088 boxes 171.9 us against 174.3;
+    // with items of one group per wave from 8 x 1200p on (79.7 against 79.8, 123.0 against 130.5)
     e = launch_pair(P, FR, ws, n_match_wgs, stream, timer, true) ? hipGetLastError() : hipErrorNotSupported;
     if (e != hipSuccess) return e;
   } else {

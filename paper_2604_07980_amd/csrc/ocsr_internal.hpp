@@ -256,6 +256,10 @@ hipError_t launch_plan_and_census(const MatchParamsDev& p, const FramesDev& fr,
                                   int sentinel, int n_cu, hipStream_t stream,
                                   const LaunchTimer* timer);
 
+// Boxes times pixels, summed over the frames: a scene's boxes grow with its image, so that the
+// blocks of a call grow about as this does.
+double match_work(const FramesDev& FR);
+
 // Multi-launch matching: the plan (unless plan_done), the matching of both levels'
 // blocks, then one aggregation workgroup per box. level_launches (OCSR_OPTION_LEVEL_LAUNCHES)
 // decides between one launch for both levels, when a kernel for the pair of variants
