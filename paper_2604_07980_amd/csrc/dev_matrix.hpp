@@ -21,8 +21,12 @@
 // offset that has the least so far; blocks share a backward pass when their forward
 // offsets are equal too.
 //
-// Bound: vector ALU. Two 8 x 8 blocks and 96 candidates take about 280 instructions and 28
-// products a direction, against 1120 for XORs and popcounts of every term.
+// Bound: vector ALU (67% busy on a batch) and, between, the latency of each group's own loads.
+// Two 8 x 8 blocks and 96 candidates take about 280 instructions and 28 products a direction,
+// against 1120 for XORs and popcounts of every term: the close level of 16 x 1200p takes 59 us
+// instead of 128. Loading a group's words and strip ahead of its mask or of its digits would
+// hide their latency but holds them through code that needs the registers: 24 to 63 spilled,
+// and 190 us instead of 130 for that batch.
 #pragma once
 
 #include "dev_fp4.hpp"

@@ -18,8 +18,8 @@ hipError_t launch_level(const MatchParamsDev& P, const FramesDev& FR, const Matc
 #define OCSR_V(ROWS, M, C)                                                                     \
   if (v.rows == ROWS && v.cpl == C)                                                            \
     return timed_launch(timer, "match",                                                       \
-                        want ? match_level_kernel<M<C>, matrix_waves<C>(), true>              \
-                             : match_level_kernel<M<C>, matrix_waves<C>(), false>,            \
+                        want ? match_level_kernel<M<C>, matrix_waves<C, true>(), true>        \
+                             : match_level_kernel<M<C>, matrix_waves<C, true>(), false>,      \
                         dim3(grid), dim3(256), 0, stream, P, FR, ws, dbg, level);
   OCSR_V(1, VQuad, 2)
   OCSR_V(1, VQuad, 4)
@@ -45,7 +45,7 @@ hipError_t launch_match_vertical(const MatchParamsDev& P, const FramesDev& FR, c
     // both levels in one launch for the usual pairs: the far blocks run beside the close ones
 #define OCSR_VP(C)                                                                            \
     if (c.cpl == C)                                                                           \
-      return timed_launch(timer, "match", match_pair2_kernel<VQuad<2>, VPair<C>, matrix_waves<C>()>, \
+      return timed_launch(timer, "match", match_pair2_kernel<VQuad<2>, VPair<C>, matrix_waves<C, true>()>, \
                           dim3(grid), dim3(256), 0, stream, P, FR, ws);
     OCSR_VP(2)
     OCSR_VP(3)

@@ -33,12 +33,15 @@ KERNEL_SOURCES = {
                "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
               "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
+              "paper_2604_07980_amd/csrc/match_kernels.hpp",
               "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match_close": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
               "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
+              "paper_2604_07980_amd/csrc/match_kernels.hpp",
                     "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "match_far": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
               "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
+              "paper_2604_07980_amd/csrc/match_kernels.hpp",
                   "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
     "plan": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
              "paper_2604_07980_amd/csrc/dev_census.hpp", "paper_2604_07980_amd/csrc/dev_common.hpp",
