@@ -33,13 +33,13 @@
 // an atomic minimum, where the strips that see the column meet.
 //
 // Bound: vector ALU (packing, 2R adds, left and right key and minimum: 2R + 5 per two
-// candidates; it issues in 82% of the cycles, the matrix cores are busy in 12%). Measured on a
-// 1920 x 1080 pair with 192 candidates, R = 2: 175 us with the check, against 225 with a pass
+// candidates; it issues in 86% of the cycles, the matrix cores are busy in 13%). Measured on a
+// 1920 x 1080 pair with 192 candidates, R = 2: 169 us with the check, against 225 with a pass
 // of its own for the right winners and 813 for the vector ALU alone (two XORs, two popcounts
-// and about six more operations a term); on a 960 x 128 region of nine offsets 67 us against
+// and about six more operations a term); on a 960 x 128 region of nine offsets 63 us against
 // 78 and 262. Bands of 10 rows measure 1.5% less on the first and 2% more on the second, of 6
-// rows 2% and 10% more; three waves per SIMD at the price of 25 spilled registers measure 10%
-// less than two; the atomics cost 2%.
+// rows 2% and 10% more; two waves per SIMD instead of three measure 10% more; the
+// atomics cost 2%.
 #include <algorithm>
 
 #include "dev_fp4.hpp"
@@ -197,9 +197,9 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
     // reaches back to in the upper half (the lower half's first 2R windows do not exist)
     uint32_t P[Z2 + 2 * R];
     auto V = [&](int z) { return __float_as_uint(acc[z / 16][z % 16]); };
+    auto pack = [&](int z) { P[2 * R + z] = __builtin_amdgcn_perm(V(z + Z2), V(z < 0 ? 0 : z), 0x05040100u); };
 #pragma unroll
-    for (int z = -2 * R; z < Z2; ++z)
-      P[2 * R + z] = __builtin_amdgcn_perm(V(z + Z2), V(z < 0 ? 0 : z), 0x05040100u);
+    for (int z = -2 * R; z < 0; ++z) pack(z);
     uint32_t key = 0xFFFFFFFFu;
 #pragma unroll
     for (int u = 0; u < NRUN; ++u) {
@@ -208,6 +208,9 @@ __device__ __forceinline__ void dense_chunk(const DenseArgs& a, int xs, int y0, 
       // the result of the instruction just before
 #pragma unroll
       for (int z8 = u * RUN; z8 < (u + 1) * RUN && z8 < Z2; z8 += 8) {
+        // (packed as they are needed: packed all at once they spilled 25 registers, 177 us)
+#pragma unroll
+        for (int v = 0; v < 8; ++v) pack(z8 + v);
         uint32_t s[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) s[v] = P[z8 + v];
