@@ -401,10 +401,13 @@ hipError_t launch_plan_and_census(const MatchParamsDev& P, const FramesDev& FR,
   const bool w34 = sx == 3 && sy == 4, w22 = sx == 2 && sy == 2, w43 = sx == 4 && sy == 3;
   const int occ = w34 ? census_list_occupancy<3, 4>() : w22 ? census_list_occupancy<2, 2>()
                   : w43 ? census_list_occupancy<4, 3>() : census_list_occupancy<-1, -1>();
-  // lists pay off once every persistent workgroup has several tiles to consider (a
-  // 1080p frame's 2550 tiles run faster one workgroup per tile, a 16-frame batch's
-  // 45600 listed)
-  if (8 * std::max(1, n_cu) * occ > n_tiles) return hipErrorNotSupported;
+  // lists pay off once every persistent workgroup has several tiles to consider, and sooner
+  // with many frames, as a frame's list is one workgroup's work. Whole calls, listed against
+  // one workgroup per tile, us: one 2160p frame (10200 tiles) 56.2 and 51.5, two (20400) 82.4
+  // and 87.6; 2 x 1200p (5700) 39.6 and 36.6, 4 (11400) 45.8 and 47.8, 6 (17100) 60.6 and 66.4;
+  // 8 x 720p (9280) 31.1 and 34.9, 8 x 600p (5840) 32.4 and 33.0
+  const int per_slot = FR.n >= 8 ? 3 : FR.n >= 4 ? 5 : 8;
+  if (per_slot * std::max(1, n_cu) * occ > n_tiles) return hipErrorNotSupported;
   hipError_t e = timed_launch(timer, "plan", plan_tiles_kernel, dim3(FR.n), dim3(256), 0, stream, P,
                               FR, boxes, ws);
   if (e != hipSuccess) return e;

@@ -53,3 +53,28 @@ def test_sizes_change_no_result(lib, n, h, w, boxes, dy):
     got = run()
     assert (got == run(OPTION_BLOCKS_PER_WAVE=1, OPTION_LEVEL_LAUNCHES=1)).all()
     assert got[:, 2].any()                      # some boxes are ranged
+
+
+# (frames, H, W): 5 and 3 tiles per resident slot of 256 compute units (7 slots each) from
+# four and eight frames on are 8960 and 5376 tiles; just below and above them
+@pytest.mark.parametrize("n, h, w", [(4, 928, 1920), (4, 1056, 1920), (8, 544, 900), (8, 608, 1000), (3, 1200, 1920)])
+def test_listed_census_changes_no_result(lib, n, h, w):
+    rng = np.random.default_rng(n * h)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(w)
+    frames, rows = [], []
+    for k in range(n):
+        left = torch.randint(0, 256, (h - k, w), dtype=torch.uint8, device=DEV, generator=gen)
+        frames.append((left, torch.roll(left, -13, 1).contiguous(), 20))
+        side = rng.integers(12, 200, (20, 2))
+        x0, y0 = rng.integers(-5, w - 12, 20), rng.integers(-5, h - 12, 20)
+        rows.append(np.stack([x0, y0, x0 + side[:, 0], y0 + side[:, 1], rng.random(20) < 0.8], 1))
+    bx = torch.from_numpy(np.concatenate(rows).astype(np.int32)).to(DEV)
+    p = synth.base_params()
+    try:
+        got = lib.range_batch(frames, bx, p).cpu().numpy()
+        lib.set_option(lib.OPTION_CENSUS_TILE_LIST, 0)
+        assert (got == lib.range_batch(frames, bx, p).cpu().numpy()).all()
+    finally:
+        lib.set_option(lib.OPTION_CENSUS_TILE_LIST, 1)
+    assert got[:, 2].any()
