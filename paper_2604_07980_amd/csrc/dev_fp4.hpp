@@ -29,10 +29,12 @@ __device__ __forceinline__ v4f mfma_fp4(v4i a, v4i b, v4f c) {
 constexpr uint32_t kSign = 0x88888888u, kOne = 0x22222222u, kTwo = 0x44444444u, kFour = 0x66666666u;
 // (w & sign) | mag and 2 w: v_bitop3_b32 and v_add_u32 issue up to 1.6 times as fast as the
 // and-or and the left shift that the compiler would take (operands in vector registers).
+// A product may read a vector instruction's result two wait states later at the earliest, and
+// the compiler keeps that distance only for instructions that it knows: what feeds a product is
+// a builtin, never inline asm (as asm, 53 of the dense kernels' 72 products followed their
+// digits too closely). Doubled words are operands of and_or alone.
 __device__ __forceinline__ uint32_t and_or(uint32_t w, uint32_t sign, uint32_t mag) {
-  uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(w), "v"(sign), "v"(mag));
-  return r;
+  return __builtin_amdgcn_bitop3_b32(w, sign, mag, 0xea);
 }
 __device__ __forceinline__ uint32_t twice(uint32_t w) {
   uint32_t r;
