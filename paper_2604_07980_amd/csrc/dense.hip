@@ -57,7 +57,8 @@ struct DenseArgs {
   int32_t d_out;              // dmin, which the winners' indices are added to (dlo is at most
                               // W + 512: from W on every candidate's word lies outside)
   int16_t* left;              // [H][W] left winners' disparity (-1: no candidate)
-  uint32_t* right;            // [H][W] right winners' cost << 16 | (d - dlo), kNoKey at first
+  uint32_t* right;            // [H][W] right winners: d - dlo in the low half, above it the cost
+                              // or (dense_few_kernel) nothing; kNoKey: no candidate
   // several pairs in one launch (grid z): pair z reads CL + z * cl_zstride (words; the
   // right image is shared) and writes left and right + z * out_zstride
   int64_t cl_zstride, out_zstride;
@@ -320,6 +321,139 @@ __global__ __launch_bounds__(256) void dense_clear_kernel(uint32_t* p, size_t n)
     for (size_t k = i; k < n; ++k) p[k] = kNoKey;
 }
 
+// A call of at most kFew candidates: no room for a chunk of the search, whose products cover 2
+// (16 T - 2R) candidate columns whatever the call asks for. The terms are formed on the vector
+// ALU instead (two XORs and two popcounts each), one view per launch and a candidate of every
+// column per step: a wave takes a strip of 64 - 2R output columns (its lanes: the strip and a
+// halo of R columns on each side) and a band of kBand output rows. Pairs of costs share a word
+// of two 16-bit halves (at most 49 x 64 = 3136 each); the vertical sums add the entering row
+// and drop the one 2R + 1 rows back (a ring in registers), 2R DPP adds finish a window.
+//
+// Bound: vector ALU. 1920 x 1080, 1 to 8 candidates, both views and the check: 44 / 53 / 59 us
+// for R = 1 / 2 / 3, where the products take 73 / 87 / 98 with T = 3 and 59 / 69 / 77 with T = 2
+// (960 x 128 of nine offsets, R = 2: 38 against 53 and 43); 9 to 16 candidates would take two
+// steps, 70 / 88 / 100 us, and the products no more than they do for one.
+constexpr int kFew = 8;
+template <int R>
+constexpr int few_strip() { return 64 - 2 * R; }
+
+__device__ __forceinline__ uint32_t shl1(uint32_t v) {   // lane i gets lane i + 1
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xF, 0xF, true);
+}
+
+// RIGHT = 0: the left view (the term at column x' pairs CL(x') with CR(x' - d)); 1: the right
+// view (the term at column x' pairs CL(x' + d) with CR(x'), and is 0 where x' + d is outside).
+// MASKED: some lane reads a word outside the image, so every word and term is checked.
+// key[o]: output row o's least cost << 8 | (d - dlo).
+template <int R, int RIGHT, bool MASKED>
+__device__ __forceinline__ void few_rows(const DenseArgs& a, int x, int y0, uint32_t (&key)[kBand]) {
+  constexpr int NW = 2 * R + 1, NR = kBand + 2 * R, NP = kFew / 2;
+  const int W = a.W;
+  // byte offsets of the fixed word and of the moving words within a row (outside the image:
+  // column 0, dropped)
+  const bool f_in = x >= 0 && x < W;
+  const uint32_t f_off = 8u * (uint32_t)(f_in ? x : 0);
+  uint32_t m_off[kFew];
+  bool m_in[kFew];
+#pragma unroll
+  for (int j = 0; j < kFew; ++j) {
+    const int xm = RIGHT ? x + a.dlo + j : x - a.dlo - j;
+    m_in[j] = xm >= 0 && xm < W;
+    m_off[j] = 8u * (uint32_t)(m_in[j] ? xm : 0);
+  }
+  // (an opaque row pitch: the rows' addresses formed one by one, not all held from the start)
+  int pitch_bytes = a.pitch * 8;
+  asm volatile("" : "+s"(pitch_bytes));
+  const char* fixed_img = (const char*)(RIGHT ? a.CR : a.CL);
+  const char* moving_img = (const char*)(RIGHT ? a.CL : a.CR);
+  uint32_t ring[NW][NP] = {}, V[NP] = {};
+  // step i is image row y0 - R + i; rows outside the image read row 0 and are dropped
+  auto load_row = [&](int i, uint64_t& f, uint64_t (&mv)[kFew]) {
+    const int yy = y0 - R + i;
+    const size_t ro = (size_t)(yy >= 0 && yy < a.H ? yy : 0) * (size_t)pitch_bytes;
+    f = *(const uint64_t*)(fixed_img + ro + f_off);
+#pragma unroll
+    for (int j = 0; j < kFew; ++j) mv[j] = *(const uint64_t*)(moving_img + ro + m_off[j]);
+  };
+  uint64_t f, mv[kFew];
+  load_row(0, f, mv);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    // step i + 1's row is loaded while step i's is summed
+    uint64_t nf = 0, nmv[kFew];
+    if (i + 1 < NR) load_row(i + 1, nf, nmv);
+    const int yy = y0 - R + i;
+    uint32_t t[NP] = {};
+    if (yy >= 0 && yy < a.H) {
+#pragma unroll
+      for (int j = 0; j < kFew; ++j) {
+        uint32_t c = (uint32_t)__popcll((!MASKED || f_in ? f : 0ull) ^ (!MASKED || m_in[j] ? mv[j] : 0ull));
+        if (MASKED && !(RIGHT ? m_in[j] : f_in)) c = 0;
+        t[j / 2] |= c << (16 * (j & 1));
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < NP; ++m) {
+      V[m] += t[m] - ring[i % NW][m];
+      ring[i % NW][m] = t[m];
+    }
+    if (i >= 2 * R) {
+      uint32_t best = 0xFFFFFFFFu;
+#pragma unroll
+      for (int m = 0; m < NP; ++m) {
+        uint32_t h = V[m], l = V[m], r = V[m];
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          l = shr1(l);
+          r = shl1(r);
+          h += l + r;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int j = 2 * m + q;
+          const uint32_t k = ((q ? h >> 16 : h & 0xFFFFu) << 8) | (uint32_t)j;
+          best = min(best, j < a.nd && (!RIGHT || !MASKED || m_in[j]) ? k : 0xFFFFFFFFu);
+        }
+      }
+      key[i - 2 * R] = best;
+    }
+    if (i + 1 < NR) {
+      f = nf;
+#pragma unroll
+      for (int j = 0; j < kFew; ++j) mv[j] = nmv[j];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// grid x: strips, y: four bands each, z: pairs. The left view's disparities, or the right view's
+// indices (every pixel is written, so that nothing needs to be cleared).
+template <int R, int RIGHT>
+__global__ __launch_bounds__(256) void dense_few_kernel(DenseArgs a) {
+  a.CL += (int64_t)blockIdx.z * a.cl_zstride;
+  a.left += (int64_t)blockIdx.z * a.out_zstride;
+  a.right += (int64_t)blockIdx.z * a.out_zstride;
+  const int lane = threadIdx.x & 63;
+  const int band = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int y0 = band * kBand;
+  if (y0 >= a.H) return;                   // whole wave; the kernel has no barrier
+  const int xw = blockIdx.x * few_strip<R>() - R;   // column of lane 0
+  const int x = xw + lane;
+  const bool inside = RIGHT ? (xw >= 0 && xw + 63 + a.dlo + kFew - 1 < a.W)
+                            : (xw - a.dlo - (kFew - 1) >= 0 && xw + 63 < a.W);
+  uint32_t key[kBand];
+  if (inside) few_rows<R, RIGHT, false>(a, x, y0, key);
+  else few_rows<R, RIGHT, true>(a, x, y0, key);
+  if (lane < R || lane >= R + few_strip<R>() || x >= a.W) return;
+#pragma unroll
+  for (int o = 0; o < kBand; ++o) {
+    const int y = y0 + o;
+    if (y >= a.H) break;
+    if (RIGHT) a.right[(size_t)y * a.W + x] = key[o] == 0xFFFFFFFFu ? kNoKey : key[o] & 0xFFu;
+    else a.left[(size_t)y * a.W + x] = (int16_t)(a.d_out + (int)(key[o] & 0xFFu));
+  }
+}
+
 // The L/R check of one row segment of 256 pixels; disp holds the left winners and receives
 // the checked ones. With `right_out` set it receives the right winners' disparities. With
 // `partial` set, the workgroup also stores how many of its checked disparities are > d_min at
@@ -376,12 +510,19 @@ __global__ __launch_bounds__(256) void count_above_kernel(const int32_t* __restr
 // the least work per output column is taken (a chunk's work: T products and reductions and
 // about 0.9 of one for the fixed column, the right winners and the row's overhead, fitted to
 // T = 3, 4 and 5 each alone at 48 to 256 candidates, where the shape taken is within 3% of the
-// best of them).
+// best of them). T = 2 is for short searches: 1920 x 1080, R = 2, 9 to 28 candidates 69 us, 32
+// 75, 36 83, against 87 with T = 3, which is taken from 40 on.
 template <int R>
 hipError_t launch_dense_r(DenseArgs a, hipStream_t s, int nz) {
+  if (a.nd <= kFew) {
+    const dim3 grid((a.W + few_strip<R>() - 1) / few_strip<R>(), (a.H + 4 * kBand - 1) / (4 * kBand), nz);
+    dense_few_kernel<R, 0><<<grid, 256, 0, s>>>(a);
+    dense_few_kernel<R, 1><<<grid, 256, 0, s>>>(a);
+    return hipGetLastError();
+  }
   int best_t = 0;
   double best = 0;
-  for (int t = 3; t <= 5; ++t) {
+  for (int t = 2; t <= 5; ++t) {
     const int per = 2 * (16 * t - 2 * R);
     for (int n = (a.nd + 7 + per - 1) / per; n <= (a.nd + 31) / per + 1; ++n) {
       const int cols = std::min(32 - 2 * R, n * per - a.nd + 1);
@@ -399,7 +540,8 @@ hipError_t launch_dense_r(DenseArgs a, hipStream_t s, int nz) {
   a.strips = (a.W + a.cols - 1) / a.cols;
   a.bands = (a.H + kBand - 1) / kBand;
   const dim3 grid((a.strips * a.bands + 3) / 4, 1, nz);
-  if (best_t == 3) dense_kernel<R, 3><<<grid, 256, 0, s>>>(a);
+  if (best_t == 2) dense_kernel<R, 2><<<grid, 256, 0, s>>>(a);
+  else if (best_t == 3) dense_kernel<R, 3><<<grid, 256, 0, s>>>(a);
   else if (best_t == 4) dense_kernel<R, 4><<<grid, 256, 0, s>>>(a);
   else dense_kernel<R, 5><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
