@@ -129,21 +129,32 @@ __device__ __forceinline__ void plan_frame(const MatchParamsDev& P, const FrameD
 // per-block steps
 // ---------------------------------------------------------------------------------
 // The first of the n running ends that passes q (the last one otherwise): one ballot per
-// 64, the loads of 256 issued together.
+// 64, the loads of 256 issued together. Above 256 ends, 64 of them that are `step` apart
+// first say between which two to look (the ends do not decrease): an item's search of 20000
+// boxes takes three loads in turn, where one through all of them took 79 and a 1080p frame of
+// that many small boxes 3.6 ms instead of 2.8 (10000: 1.47 instead of 1.18 ms).
 __device__ __forceinline__ int find_box(const int32_t* __restrict__ end, int n, int q, int lane) {
-  for (int base = 0; base < n; base += 256) {
-    int e[4];
+  int first = 0, left = n;                      // the answer is among ends first .. first + left - 1
+  while (left > 256) {
+    const int step = (left + 63) >> 6;
+    const int at = min(step * (lane + 1), left) - 1;
+    const uint64_t m = __ballot(end[first + at] > q);
+    if (!m) return n - 1;
+    const int k = __ffsll((unsigned long long)m) - 1;
+    first += step * k;
+    left = min(step, left - step * k);
+  }
+  int e[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = base + 64 * u + lane;
-      e[u] = 0x7FFFFFFF;
-      if (base + 64 * u < n && i < n) e[u] = end[i];
-    }
+  for (int u = 0; u < 4; ++u) {
+    const int i = 64 * u + lane;
+    e[u] = 0x7FFFFFFF;
+    if (64 * u < left && i < left) e[u] = end[first + i];
+  }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint64_t m = __ballot(e[u] > q);
-      if (m) return min(base + 64 * u + __ffsll((unsigned long long)m) - 1, n - 1);
-    }
+  for (int u = 0; u < 4; ++u) {
+    const uint64_t m = __ballot(e[u] > q);
+    if (m) return min(first + 64 * u + __ffsll((unsigned long long)m) - 1, n - 1);
   }
   return n - 1;
 }
