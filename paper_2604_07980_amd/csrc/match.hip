@@ -437,7 +437,7 @@ hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (P.vertical) {
-    e = launch_match_vertical(P, FR, ws, dbg, n_match_wgs, stream, timer);
+    e = launch_match_vertical(P, FR, ws, dbg, n_match_wgs, level_launches, stream, timer);
     if (e != hipSuccess) return e;
   } else if (!dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd &&
              (level_launches == 2 ||

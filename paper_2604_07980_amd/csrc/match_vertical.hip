@@ -37,11 +37,11 @@ hipError_t launch_level(const MatchParamsDev& P, const FramesDev& FR, const Matc
 }  // namespace
 
 hipError_t launch_match_vertical(const MatchParamsDev& P, const FramesDev& FR, const MatchWs& ws,
-                                 const DebugDev& dbg, int grid, hipStream_t stream,
-                                 const LaunchTimer* timer) {
+                                 const DebugDev& dbg, int grid, int level_launches,
+                                 hipStream_t stream, const LaunchTimer* timer) {
   const PathDev& f = P.path[0];
   const PathDev& c = P.path[1];
-  if (!dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd && f.rows == 1 && f.cpl == 2 && c.rows == 2) {
+  if (level_launches != 1 && !dbg.blocks && !dbg.cost_fwd && !dbg.cost_bwd && f.rows == 1 && f.cpl == 2 && c.rows == 2) {
     // both levels in one launch for the usual pairs: the far blocks run beside the close ones
 #define OCSR_VP(C)                                                                            \
     if (c.cpl == C)                                                                           \

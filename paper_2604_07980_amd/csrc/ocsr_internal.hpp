@@ -269,10 +269,10 @@ hipError_t launch_match(const MatchParamsDev& p, const FramesDev& fr, const ocsr
                         bool plan_done, int n_match_wgs, int level_launches, hipStream_t stream,
                         const LaunchTimer* timer);
 
-// The matching launches of a call with a vertical range.
+// The matching launches of a call with a vertical range (level_launches as in launch_match).
 hipError_t launch_match_vertical(const MatchParamsDev& p, const FramesDev& fr, const MatchWs& ws,
-                                 const DebugDev& dbg, int n_match_wgs, hipStream_t stream,
-                                 const LaunchTimer* timer);
+                                 const DebugDev& dbg, int n_match_wgs, int level_launches,
+                                 hipStream_t stream, const LaunchTimer* timer);
 
 // Fused path: census of every frame, planning, matching and aggregation in one
 // persistent launch of co-resident workgroups (after a counter reset). Returns
