@@ -311,10 +311,12 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
       return fail(OCSR_E_UNSUPPORTED, "%s path: %d disparities x %d vertical offsets need %zu bytes of "
                   "LDS per workgroup > %zu", l == 0 ? "far" : "close", ph.nd, ph.ndy, lds, kDyMaxWgLds);
     // the matrix-core matchers serve every vertical range, whatever variant was chosen: four
-    // 4 x 4 blocks per wave up to 64 candidates, else two blocks per wave
-    ph.rows = rows == 4 && ph.nd <= 64 ? 1 : 2;
-    ph.cpl = ph.rows == 1 ? (ph.nd <= 32 ? 2 : 4) : (ph.nd + 31) / 32;
-    if (ph.cpl == 7) ph.cpl = 8;
+    // 4 x 4 blocks per wave, or two blocks per wave (160 candidates at most, see above). Small
+    // blocks two to a wave leave half of its digits empty: 1080p, 100 boxes, close 4 x 4,
+    // dy -1..1, us with two and with four: 76 and 53 over 128 candidates, 111 and 72 over 192,
+    // 154 and 92 over 256 (8 boxes: 36 and 34, 42 and 38, 52 and 46)
+    ph.rows = rows == 4 ? 1 : 2;
+    ph.cpl = rows == 4 ? (ph.nd <= 32 ? 2 : ph.nd <= 64 ? 4 : ph.nd <= 128 ? 8 : ph.nd <= 192 ? 12 : 16) : (ph.nd + 31) / 32;
     ph.passes = 1;
   }
   if (p->lr_tol < 0) return fail(OCSR_E_INVALID, "lr_tol < 0");

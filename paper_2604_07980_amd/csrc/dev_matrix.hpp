@@ -44,7 +44,9 @@ struct Matrix {
   static constexpr int NC = LB * CPL;           // candidates
   static constexpr int T = NC / 16 + 1;         // tiles of 16 strip columns: NC + 15 are read
   static constexpr int TB = T + 1;              // of a wide backward pass
-  static constexpr int VS = 10;                 // LDS words per strip column: 8 and padding
+  // LDS words per strip column: 8 and padding (9 words share a bank among half as many of the
+  // lanes of a block, CPL columns apart, where CPL is a multiple of 4)
+  static constexpr int VS = NB == 4 && CPL >= 8 ? 9 : 10;
   // V (16 TB columns), then the forward costs of the NB blocks
   static constexpr int kCostAt = 16 * TB * VS;
   static constexpr size_t kLdsBytes = sizeof(uint32_t) * (kCostAt + NB * NC);
@@ -158,7 +160,9 @@ __device__ __forceinline__ void strip_sums(const uint64_t* __restrict__ img, con
     uint2 v;
     v.x = __builtin_amdgcn_perm(bits(1), bits(0), 0x05040100u);
     v.y = __builtin_amdgcn_perm(bits(3), bits(2), 0x05040100u);
-    *(uint2*)(V + (16 * t + n) * M::VS + 2 * kq) = v;
+    uint32_t* to = V + (16 * t + n) * M::VS + 2 * kq;
+    if constexpr (M::VS % 2 == 0) *(uint2*)to = v;
+    else __builtin_memcpy(to, &v, 8);
   };
   // (tile by tile: a tile's digits live for its own products only. Digit group by digit
   // group, with independent products in a row, spills: 137 against 128 us on the batch)
