@@ -481,9 +481,10 @@ int32_t ocsr_rect_filter_update(ocsr_rect_filter* f, const int32_t* counts, int3
  * launch (1..64, default 16). The launch deals its work items over this grid. */
 #define OCSR_OPTION_MATCH_WGS_PER_CU 4
 /* OCSR_OPTION_BLOCKS_PER_WAVE: blocks each wave of a matching workgroup takes per work
- * item (1..8; until it is set 1, 2 or 3 by the call's boxes and image sizes); a work item
- * holds 4 x this many blocks of one box. A variant whose waves take several adjacent blocks
- * together (rows = 1 or 2 below) counts those as one. */
+ * item (1..8; 0, the default: 1, 2 or 3 by the call's boxes and image sizes); a work item
+ * holds 4 x this many blocks of one box. A variant whose waves take two adjacent blocks
+ * together (rows = 2 below) counts those as one; one that takes four (rows = 1) always takes
+ * one such group per work item. */
 #define OCSR_OPTION_BLOCKS_PER_WAVE 5
 /* OCSR_OPTION_GRAPH: 1 submits whole-frame and batch calls (ocsr_range_frame,
  * ocsr_range_batch) as HIP graphs: the first call with a given set of arguments

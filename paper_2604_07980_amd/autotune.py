@@ -20,9 +20,9 @@ from dataclasses import dataclass, field
 
 from . import ocsr
 
-BLOCKS_PER_WAVE = (1, 2, 4)
+BLOCKS_PER_WAVE = (0, 1, 2, 3, 4)      # 0: by the call's size
 MATCH_WGS_PER_CU = (4, 8, 16, 32)
-DEFAULT_BLOCKS_PER_WAVE = 1
+DEFAULT_BLOCKS_PER_WAVE = 0
 DEFAULT_MATCH_WGS_PER_CU = 16
 
 
@@ -192,7 +192,7 @@ def from_json(text: str) -> Table:
         bw, bh = (int(x) for x in bw_bh.split("x"))
         if len(v) != 3 or tuple(v) not in ocsr.variant_candidates(bw, bh, int(nd)):
             raise ValueError(f"table entry {key}: no kernel {v} (rows, cpl, passes) covers it")
-    if not 1 <= t.blocks_per_wave <= 8 or not 1 <= t.match_wgs_per_cu <= 64 or t.level_launches not in (0, 1, 2):
+    if not 0 <= t.blocks_per_wave <= 8 or not 1 <= t.match_wgs_per_cu <= 64 or t.level_launches not in (0, 1, 2):
         raise ValueError("table launch settings out of range")
     return t
 

@@ -931,8 +931,8 @@ int32_t ocsr_ctx_set_option(ocsr_ctx* ctx, int32_t option, int32_t value) {
       ctx->match_wgs_per_cu = value;
       return OCSR_OK;
     case OCSR_OPTION_BLOCKS_PER_WAVE:
-      if (value < 1 || value > kMaxBlocksPerWave)
-        return fail(OCSR_E_INVALID, "blocks per wave outside 1..%d", kMaxBlocksPerWave);
+      if (value < 0 || value > kMaxBlocksPerWave)
+        return fail(OCSR_E_INVALID, "blocks per wave outside 0..%d", kMaxBlocksPerWave);
       ctx->blocks_per_wave = value;
       return OCSR_OK;
     case OCSR_OPTION_FULL_CENSUS:
