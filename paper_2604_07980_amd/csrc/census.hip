@@ -14,7 +14,7 @@ __device__ __forceinline__ int find_job(const CensusJobsDev& jobs, int tile) {
 
 template <int SX, int SY>
 __global__ __launch_bounds__(256) void census_kernel(CensusJobsDev jobs, int sentinel) {
-  __shared__ uint32_t P[dev::CensusTile<SX, SY>::kLdsBytes / sizeof(uint32_t)];
+  __shared__ alignas(dev::kCensusLdsAlign) uint32_t P[dev::CensusTile<SX, SY>::kLdsBytes / sizeof(uint32_t)];
   const CensusJobDev& jb = jobs.job[find_job(jobs, blockIdx.x)];
   const int t = blockIdx.x - jb.tile_begin;
   dev::census_tile<SX, SY>(jb.img, jb.W, jb.H, jb.pitch, jb.scale, jb.out, jb.out_pitch,

@@ -23,6 +23,9 @@
 namespace ocsr {
 namespace dev {
 
+// alignment of the LDS that a tile is made in
+constexpr size_t kCensusLdsAlign = 16;
+
 constexpr int kCensusRowsPerLane = 2;   // 4 waves x 4 lane groups x 2 rows = kCensusTileY
 
 template <int SX, int SY>
@@ -37,6 +40,7 @@ struct CensusTile {
   static constexpr int kOutAt = LP * LR;
   static constexpr size_t kLdsBytes = sizeof(uint32_t) * (kOutAt + 4 * 512);
   static_assert(N + 1 <= 64, "window wider than a 64-bit code");
+  static_assert(kOutAt % 4 == 0, "codes change lanes in 16-byte accesses (kCensusLdsAlign)");
   static_assert(SX <= 4 && LW <= LP, "a lane's window row is at most three words");
 };
 

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void fused_kernel(MatchParamsDev P, FramesDev 
   constexpr size_t kPlan = sizeof(uint32_t) * kFrameTileWords + sizeof(int) * 8;
   constexpr size_t kLds = cmax(cmax(cmax(dev::CensusTile<CSX, CSY>::kLdsBytes, kPlan), kItemWaves * kWave),
                                sizeof(dev::AggLds));
-  __shared__ uint64_t lds[(kLds + 7) / 8];
+  __shared__ alignas(dev::kCensusLdsAlign) uint64_t lds[(kLds + 7) / 8];
   __shared__ int mprefix[2 * kMaxFrames + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -24,7 +24,7 @@ template <int SX, int SY>
 __global__ __launch_bounds__(256) void frame_census_kernel(MatchParamsDev P, FramesDev FR,
                                                            const ocsr_box* boxes, MatchWs ws,
                                                            int sx, int sy, int sentinel) {
-  __shared__ uint32_t lds[SX >= 0 ? dev::CensusTile<(SX > 0 ? SX : 0), (SY > 0 ? SY : 0)>::kLdsBytes / 4 : 1];
+  __shared__ alignas(dev::kCensusLdsAlign) uint32_t lds[SX >= 0 ? dev::CensusTile<(SX > 0 ? SX : 0), (SY > 0 ? SY : 0)>::kLdsBytes / 4 : 1];
   __shared__ int tsc[4];
   if ((int)blockIdx.x < FR.n) {
     if (threadIdx.x < 64)
@@ -69,7 +69,7 @@ template <int SX, int SY>
 __global__ __launch_bounds__(256) void census_list_kernel(MatchParamsDev P, FramesDev FR,
                                                           const ocsr_box* boxes, MatchWs ws,
                                                           int sx, int sy, int sentinel) {
-  __shared__ uint32_t lds[SX >= 0 ? dev::CensusTile<(SX > 0 ? SX : 0), (SY > 0 ? SY : 0)>::kLdsBytes / 4 : 1];
+  __shared__ alignas(dev::kCensusLdsAlign) uint32_t lds[SX >= 0 ? dev::CensusTile<(SX > 0 ? SX : 0), (SY > 0 ? SY : 0)>::kLdsBytes / 4 : 1];
   __shared__ int pre[kMaxFrames + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < 64) {
