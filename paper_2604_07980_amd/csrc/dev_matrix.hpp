@@ -55,14 +55,16 @@ struct Matrix {
 
 // The point masks and occluders of a group: lane o of co holds the o-th rectangle that may
 // hide points of the box (bit o of cand). With more than 64 of them in_lanes is false and
-// the frame's boxes are scanned for every group.
+// the frame's boxes are scanned for every group; with more than 64 boxes in the frame and one
+// group to a wave that scan is the only one.
 __device__ __forceinline__ OccLanes box_occluders(const OccLanes& frame, const MatchWs& ws, int box_off,
-                                                  int n, int k, int lane, void* lds) {
+                                                  int n, int k, bool one_group, int lane, void* lds) {
   OccLanes oc = frame;
   if (n <= 64) {
     box_candidates(oc, n, k, lane);
     return oc;
   }
+  if (one_group) return oc;                     // (in_lanes is false)
   const BoxClip ck = ws.clip[box_off + k];
   BoxClip* list = (BoxClip*)lds;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -96,19 +98,33 @@ __device__ __forceinline__ OccLanes box_occluders(const OccLanes& frame, const M
   return oc;
 }
 
-// Whether point (fx, fy) of box k lies in an occluder, all boxes of the frame scanned.
-__device__ __forceinline__ bool scan_hidden(const MatchWs& ws, int box_off, int n, int k, int fx, int fy,
-                                            int lane) {
+// Whether points (fx[q], fy) of box k lie in an occluder, all boxes of the frame scanned for those
+// that meet the group's rectangle [bx0, bx1] x [by0, by1] (a crowded frame's boxes have hundreds
+// of occluders, a group's rectangle few).
+template <int NM>
+__device__ __forceinline__ void scan_hidden(const MatchWs& ws, int box_off, int n, int k, int bx0, int bx1,
+                                            int by0, int by1, const int (&fx)[NM], int fy, int lane,
+                                            bool (&hidden)[NM]) {
   const BoxClip ck = ws.clip[box_off + k];
-  bool hidden = false;
-  for (int jb = 0; jb < n; jb += 64) {
-    const int o = jb + lane;
-    const BoxClip co = o < n ? ws.clip[box_off + o] : BoxClip{0, 0, 0, 0};
-    const bool occ = o < n && o != k && ck.cx0 < co.cx1 && co.cx0 < ck.cx1 && ck.cy0 < co.cy1 &&
-                     co.cy0 < ck.cy1 && co.cy1 > ck.cy1;
-    hidden |= in_lane_rects(__ballot(occ), co, fx, fy);
+  for (int jb = 0; jb < n; jb += 256) {
+    BoxClip co[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int o = jb + 64 * u + lane;
+      co[u] = BoxClip{0, 0, 0, 0};
+      if (o < n) co[u] = ws.clip[box_off + o];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int o = jb + 64 * u + lane;
+      const bool occ = o < n && o != k && ck.cx0 < co[u].cx1 && co[u].cx0 < ck.cx1 && ck.cy0 < co[u].cy1 &&
+                       co[u].cy0 < ck.cy1 && co[u].cy1 > ck.cy1 && co[u].cx0 <= bx1 && co[u].cx1 > bx0 &&
+                       co[u].cy0 <= by1 && co[u].cy1 > by0;
+      const uint64_t m = __ballot(occ);
+#pragma unroll
+      for (int q = 0; q < NM; ++q) hidden[q] |= in_lane_rects(m, co[u], fx[q], fy);
+    }
   }
-  return hidden;
 }
 
 // Column sums of the group against 16 T (wide: 16 TB) strip columns from x_first on, into
@@ -236,22 +252,28 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
   constexpr int NM = NB * BS * BS / 64;         // ballots: 2 (a block each) or 1 (four blocks)
   uint64_t mask[NM];
   {
-    uint64_t m = 0;
-    if (oc.in_lanes) {
-      const BoxClip co = oc.co;
-      const bool occ = ((oc.cand >> lane) & 1ull) && co.cx0 <= s * (X0 + nb * nx - 1) && co.cx1 > s * X0 &&
-                       co.cy0 <= s * (Y0 + ny - 1) && co.cy1 > s * Y0;
-      m = __ballot(occ);
-    }
+    const int bx0 = s * X0, bx1 = s * (X0 + nb * nx - 1), by0 = s * Y0, by1 = s * (Y0 + ny - 1);
     const int pi = lane & (BS - 1), pj = (lane / BS) & (BS - 1), pb = lane / (BS * BS);
+    const int fy = s * (Y0 + pj);
+    int fx[NM];
+    bool hidden[NM];
 #pragma unroll
     for (int q = 0; q < NM; ++q) {
-      const int b = q + pb;
-      const int fx = s * (X0 + b * nx + pi), fy = s * (Y0 + pj);
-      const bool hidden = oc.in_lanes ? in_lane_rects(m, oc.co, fx, fy)
-                                      : scan_hidden(ws, fr.box_off, fr.n_boxes, r.k, fx, fy, lane);
-      mask[q] = __ballot(b < nb && pi < nx && pj < ny && !hidden);
+      fx[q] = s * (X0 + (q + pb) * nx + pi);
+      hidden[q] = false;
     }
+    if (oc.in_lanes) {
+      const BoxClip co = oc.co;
+      const bool occ = ((oc.cand >> lane) & 1ull) && co.cx0 <= bx1 && co.cx1 > bx0 && co.cy0 <= by1 &&
+                       co.cy1 > by0;
+      const uint64_t m = __ballot(occ);
+#pragma unroll
+      for (int q = 0; q < NM; ++q) hidden[q] = in_lane_rects(m, co, fx[q], fy);
+    } else {
+      scan_hidden<NM>(ws, fr.box_off, fr.n_boxes, r.k, bx0, bx1, by0, by1, fx, fy, lane, hidden);
+    }
+#pragma unroll
+    for (int q = 0; q < NM; ++q) mask[q] = __ballot(q + pb < nb && pi < nx && pj < ny && !hidden[q]);
   }
   auto block_mask16 = [&](int b) {              // block b's mask
     if constexpr (NB == 2) return mask[b];
@@ -480,7 +502,8 @@ struct MatrixMatcher {
                                                   const MatchWs& ws, const DebugDev& dbg, int f,
                                                   int level, const ItemRec& r, int wave, int lane,
                                                   void* lds, const State& st) {
-    const OccLanes oc = box_occluders(st, ws, fr.box_off, fr.n_boxes, r.k, lane, lds);
+    const OccLanes oc = box_occluders(st, ws, fr.box_off, fr.n_boxes, r.k,
+                                      P.item_blocks[level] <= kItemWaves, lane, lds);
     const int ngx = (r.nbx + NB - 1) / NB;      // groups per block row
     int g = r.first + wave;
     int v = g / ngx, ug = g - v * ngx;
