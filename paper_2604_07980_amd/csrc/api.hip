@@ -361,6 +361,15 @@ void deal_items(const ocsr_ctx* ctx, const FramesDev& FR, bool fused, MatchParam
   const int by_size = fused ? 1 : d->vertical ? (work < 900e6 ? 1 : 2) : work < 240e6 ? 1 : work < 900e6 ? 2 : 3;
   const int n = ctx->blocks_per_wave > 0 ? ctx->blocks_per_wave : by_size;
   for (int l = 0; l < 2; ++l) d->item_blocks[l] = kItemWaves * (d->group_x[l] == 4 ? 1 : n);
+  // A group's vertical offsets by four waves instead of one, in launches of at most 2048 groups:
+  // with fewer groups than that much of the GPU waits for the longest walk over the offsets, with
+  // more every wave has a walk of its own and sharing only repeats a group's masks and digits.
+  // us without and with it, and with limits of 1024 and 4096 groups:
+  //   480p, 8 boxes, dy -3..3      40.6 / 29.5, 29.9, 29.6    1080p, 64, dy -3..3  52.4 / 44.6, 51.5, 44.6
+  //   2160p, 40, dy -3..3          50.5 / 43.8, 43.3, 43.5    4 x 1200p, 40, -1..1 64.3 / 62.4, 62.8, 81.0
+  if (d->vertical && d->item_blocks[0] == kItemWaves && d->item_blocks[1] == kItemWaves &&
+      std::max(d->path[0].ndy, d->path[1].ndy) > 1)
+    d->share_groups = 2048;
 }
 
 DebugDev make_debug(const ocsr_debug* dbg) {

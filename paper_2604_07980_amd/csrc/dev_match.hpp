@@ -169,6 +169,7 @@ __device__ __forceinline__ ItemRec find_item(const MatchParamsDev& P, const Fram
   const BoxPlan pl = ws.plan[fr.box_off + k];
   ItemRec r;
   r.k = k;
+  r.sub = -1;
   r.first = uniform((q - pl.ioff) * P.item_blocks[level]);
   r.nblk = uniform(pl.nblk); r.ngrp = uniform(block_groups(pl.nbx, pl.nby, P.group_x[level])); r.off = uniform(pl.off);
   r.nbx = uniform(pl.nbx); r.bw = uniform(pl.bw); r.bh = uniform(pl.bh);
@@ -807,23 +808,33 @@ __device__ __forceinline__ void run_item_rec(const MatchParamsDev& P, const Fram
   }
 }
 
+// log2 of the units that an item of kItemWaves groups is dealt in: one, or kItemWaves where the
+// call's n items hold at most share_groups groups (0: never).
+__device__ __forceinline__ int share_items(int n, int share_groups) {
+  static_assert(kItemWaves == 4, "units of a quarter");
+  return n <= share_groups / kItemWaves ? (share_groups > 0 ? 2 : 0) : 0;
+}
+
 // Loop of a workgroup over the work items of one level of every frame (frames in
 // order, each frame's items in box order), dealt XCD by XCD (xcd_deal). Item numbers
 // come from the workgroup index, so the loop is uniform across the workgroup and needs
-// no shared counter. body(f, q) gets the frame and the item number within the frame's
-// level.
+// no shared counter. body(f, q, sub) gets the frame, the item number within the frame's
+// level and -1; or, where the items hold at most share_groups groups (kItemWaves each), the
+// items' groups are dealt one by one and sub is the group's number within its item.
 template <class Body>
 __device__ __forceinline__ void level_items(const FramesDev& FR, const MatchWs& ws, int level,
-                                            Body body) {
+                                            int share_groups, Body body) {
   const int lane = threadIdx.x & 63;
   const int cnt = lane < FR.n ? ws.fcount[lane * FC_N + (level == 0 ? FC_FAR_ITEMS : FC_CLOSE_ITEMS)] : 0;
   const int incl = wave_incl_scan(cnt);
   const int total = __builtin_amdgcn_readlane(incl, 63);
-  const Deal dl = xcd_deal(total);
-  for (int q = dl.first; q < dl.end; q += dl.step) {
+  const int sh = share_items(total, share_groups);
+  const Deal dl = xcd_deal(total << sh);
+  for (int i = dl.first; i < dl.end; i += dl.step) {
+    const int q = i >> sh;
     const uint64_t m = __ballot(lane < FR.n && incl > q);
     const int f = __ffsll((unsigned long long)m) - 1;
-    body(f, q - __builtin_amdgcn_readlane(incl - cnt, f));
+    body(f, q - __builtin_amdgcn_readlane(incl - cnt, f), sh ? i & (kItemWaves - 1) : -1);
   }
 }
 
@@ -1394,6 +1405,7 @@ struct NoFrameState {};
 template <int ROWS, int NX, int CPL, int PASSES>
 struct TiledMatcher {
   static constexpr size_t kLds = (Tiled<ROWS, NX, CPL, PASSES>::kLdsBytes + 15) & ~(size_t)15;
+  static constexpr bool kShares = false;
   using State = NoFrameState;
   static __device__ __forceinline__ State frame_state(const MatchWs&, const FrameDev&, int) { return {}; }
   static __device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr,
@@ -1408,6 +1420,7 @@ struct TiledMatcher {
 // any block of up to 64 points (GRID blocks included), lanes over candidates
 struct GenericMatcher {
   static constexpr size_t kLds = (kGenericLdsBytes + 15) & ~(size_t)15;
+  static constexpr bool kShares = false;
   using State = NoFrameState;
   static __device__ __forceinline__ State frame_state(const MatchWs&, const FrameDev&, int) { return {}; }
   static __device__ __forceinline__ void run_item(const MatchParamsDev& P, const FrameDev& fr,

@@ -19,7 +19,8 @@
 // With a vertical range (the census cost over (dx, dy), Sec. 4.3.2) each direction repeats
 // the strip for every vertical offset, its rows moved by one, and keeps the costs of the
 // offset that has the least so far; blocks share a backward pass when their forward
-// offsets are equal too.
+// offsets are equal too. In calls of few groups the four waves of a workgroup take one group
+// together, every fourth offset each, and the least of their keys wins.
 //
 // Bound: vector ALU (67% busy on a batch) and, between, the latency of each group's own loads.
 // Two 8 x 8 blocks and 96 candidates take about 280 instructions and 28 products a direction,
@@ -236,7 +237,8 @@ __device__ __forceinline__ uint32_t block_min(uint32_t v, int lane) {
 template <int NB, int CPL, bool VERT>
 __device__ __forceinline__ void match_group(const MatchParamsDev& P, const FrameDev& fr, const MatchWs& ws,
                                             const DebugDev& dbg, int f, int level, const ItemRec& r,
-                                            int u, int v, const OccLanes& oc, int lane, void* lds) {
+                                            int u, int v, const OccLanes& oc, int wave, int lane,
+                                            void* lds) {
   using M = Matrix<NB, CPL>;
   constexpr int BS = M::BS, G = M::G, LB = M::LB, NC = M::NC;
   uint32_t* V = (uint32_t*)lds;
@@ -245,6 +247,9 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
   const PathDev& ph = P.path[level];
   const int nd = ph.nd, dlo = ph.dlo, dhi = dlo + nd - 1;
   const int ndy = VERT ? ph.ndy : 1, dylo = VERT ? ph.dylo : 0;
+  // the offsets that this wave walks: all, or every fourth from its own number on
+  const bool share = VERT && r.sub >= 0;
+  const int ey0 = share ? wave : 0, ey_step = share ? kItemWaves : 1;
   const int nx = r.bw, ny = r.bh, s = lv.scale;
   const int nb = min(NB, r.nbx - u);
   const int X0 = r.ox + u * nx, Y0 = r.oy + v * ny;
@@ -290,7 +295,8 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
   const int m = lane & 15, kq = lane >> 4, tb = m / BS, ti = m & (BS - 1);
   const int b = lane / LB, e0 = CPL * (lane & (LB - 1));
   const int slot = f * P.cap_blocks + r.off + v * r.nbx + u + b;
-  const bool writer = (lane & (LB - 1)) == 0 && b < nb;
+  const bool lead = (lane & (LB - 1)) == 0;
+  const bool writer = lead && b < nb && (!share || wave == 0);
   const bool mine = (eligible >> b) & 1u;       // this lane's block is eligible
   uint32_t keep[G];                             // all ones where the lane's point counts
 #pragma unroll
@@ -353,7 +359,7 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
     // ndy + (dy - dylo)
     uint32_t cost[CPL];
     uint32_t key = 0xFFFFFFFFu;
-    for (int ey = 0; ey < ndy; ++ey) {
+    for (int ey = ey0; ey < ndy; ey += ey_step) {
       strip_sums<M, VERT>(lv.R, lv, X0 - dhi, Y0 + dylo + ey, ny, false, a, V, lane);
       wave_sync();
       diagonal_costs<M>(V, b, b * nx + e0, cost);
@@ -375,15 +381,38 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
       if (VERT) wave_sync();
     }
     if (want_costs && dbg.cost_fwd) put_costs(dbg.cost_fwd, rest(t));
-    const int id = (int)(key & 0xFFFFu);
-    const int best = VERT ? id / ndy : id;
-    d_f = dlo + best;
-    if (VERT) dy_f = dylo + id - best * ndy;
+    int id = (int)(key & 0xFFFFu);
+    int best = VERT ? min(id / ndy, nd - 1) : id;   // (a wave without offsets has no key)
     wave_sync();
     // the parabola's numerator and denominator are both twice those of the Hamming sums, and
     // their quotient the same number
-    const int ca = (int)costf[b * NC + max(best - 1, 0)];
-    const int cb = (int)costf[b * NC + min(best + 1, nd - 1)];
+    int ca = (int)costf[b * NC + max(best - 1, 0)];
+    int cb = (int)costf[b * NC + min(best + 1, nd - 1)];
+    if constexpr (VERT) {
+      if (share) {
+        // the least key of the four waves, and the costs beside it
+        __shared__ uint32_t best_of[kItemWaves][NB][3];
+        if (lead) {
+          best_of[wave][b][0] = key;
+          best_of[wave][b][1] = (uint32_t)ca;
+          best_of[wave][b][2] = (uint32_t)cb;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kItemWaves; ++w) {
+          const uint32_t k = best_of[w][b][0];
+          if (k <= key) {
+            key = k;
+            ca = (int)best_of[w][b][1];
+            cb = (int)best_of[w][b][2];
+          }
+        }
+        id = (int)(key & 0xFFFFu);
+        best = id / ndy;
+      }
+      dy_f = dylo + id - best * ndy;
+    }
+    d_f = dlo + best;
     if (mine) d_sub = subpixel(d_f, best, nd, ca, (int)(key >> 16), cb);
 
     // backward: the group's columns are CR(x - d_f) in rows y + dy_f, candidate e of block b is
@@ -436,7 +465,7 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
       }
       left &= ~now;
       const bool here = (now >> b) & 1u;
-      for (int ey = 0; ey < ndy; ++ey) {
+      for (int ey = ey0; ey < ndy; ey += ey_step) {
         strip_sums<M, VERT>(lv.L, lv, base, VERT ? Y0 + bdy - dylo - ey : Y0, ny, far > 16 - BS, a, V, lane);
         wave_sync();
         diagonal_costs<M>(V, b, off + e0, cost);
@@ -456,6 +485,15 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
       }
     }
     if (!VERT) bkey = block_min<LB>(bkey, lane);
+    if constexpr (VERT) {
+      if (share) {
+        __shared__ uint32_t bkey_of[kItemWaves][NB];
+        if (lead) bkey_of[wave][b] = bkey;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kItemWaves; ++w) bkey = min(bkey, bkey_of[w][b]);
+      }
+    }
     if (want_costs && dbg.cost_bwd) put_costs(dbg.cost_bwd, rest(t));
     const int bid = (int)(bkey & 0xFFFFu);
     const int bb = VERT ? bid / ndy : bid;
@@ -490,10 +528,13 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
 }
 
 // Matcher of one level's TILED blocks: wave w of a workgroup takes groups r.first + w,
-// r.first + w + 4, ... of an item.
+// r.first + w + 4, ... of an item; or, where the waves share a group's vertical offsets (r.sub >=
+// 0), all four take group r.first + r.sub. Everything that decides the way to match_group's
+// barriers is the same for the four waves: the item, the box, the group's point masks.
 template <int NB, int CPL, bool VERT = false>
 struct MatrixMatcher {
   static constexpr size_t kLds = (Matrix<NB, CPL>::kLdsBytes + 15) & ~(size_t)15;
+  static constexpr bool kShares = VERT;         // a group's offsets may be shared
   using State = OccLanes;
   static __device__ __forceinline__ State frame_state(const MatchWs& ws, const FrameDev& fr, int lane) {
     return frame_lanes(ws, fr.box_off, fr.n_boxes, lane);
@@ -503,12 +544,13 @@ struct MatrixMatcher {
                                                   int level, const ItemRec& r, int wave, int lane,
                                                   void* lds, const State& st) {
     const OccLanes oc = box_occluders(st, ws, fr.box_off, fr.n_boxes, r.k,
-                                      P.item_blocks[level] <= kItemWaves, lane, lds);
+                                      P.item_blocks[level] <= kItemWaves || r.sub >= 0, lane, lds);
     const int ngx = (r.nbx + NB - 1) / NB;      // groups per block row
-    int g = r.first + wave;
+    const bool share = VERT && r.sub >= 0;
+    int g = r.first + (share ? r.sub : wave);
     int v = g / ngx, ug = g - v * ngx;
-    for (int j = wave; j < P.item_blocks[level]; j += kItemWaves) {
-      if (g < r.ngrp) match_group<NB, CPL, VERT>(P, fr, ws, dbg, f, level, r, NB * ug, v, oc, lane, lds);
+    for (int j = share ? 0 : wave; j < (share ? 1 : P.item_blocks[level]); j += kItemWaves) {
+      if (g < r.ngrp) match_group<NB, CPL, VERT>(P, fr, ws, dbg, f, level, r, NB * ug, v, oc, wave, lane, lds);
       g += kItemWaves;
       ug += kItemWaves;
       while (ug >= ngx) {

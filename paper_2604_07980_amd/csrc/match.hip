@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tiled_waves
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   void* wl = (char*)lds + wave * kWave;
-  dev::level_items(FR, ws, level, [&](int f, int q) {
+  dev::level_items(FR, ws, level, 0, [&](int f, int q, int) {
     const FrameDev& fr = FR.f[f];
     const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
     dev::run_item_rec(P, fr, f, level, r, wave, [&](const dev::BlockCtx& c) {

@@ -29,10 +29,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
   __syncthreads();
   void* wl = (char*)lds + wave * kWave;
   // the close items of every frame, then the far ones, dealt XCD by XCD as two lists
-  const int n_close = prefix[F];
-  const dev::Deal2 dl = dev::xcd_deal2(n_close, prefix[2 * F] - n_close);
+  const int n_close = prefix[F], n_all = prefix[2 * F];
+  const int sh = dev::share_items(n_all, FM::kShares && CM::kShares ? P.share_groups : 0);
+  const dev::Deal2 dl = dev::xcd_deal2(n_close << sh, (n_all - n_close) << sh);
   for (int i = dl.first; i < dl.end; i += dl.step) {
-    const int m = dl.at(i);
+    const int at = dl.at(i), m = at >> sh;
+    const int sub = sh ? at & (kItemWaves - 1) : -1;
     int slot = 0;
     for (int k = 1; k < 2 * F; ++k)
       if (m >= prefix[k]) slot = k;
@@ -45,11 +47,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     asm volatile("" : "+v"(il));
     if (slot < F) {
       const typename CM::State st = CM::frame_state(ws, fr, il);
-      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 1, q, il);
+      ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 1, q, il);
+      r.sub = sub;
       CM::run_item(P, fr, ws, dbg, f, 1, r, wave, il, wl, st);
     } else {
       const typename FM::State st = FM::frame_state(ws, fr, il);
-      const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 0, q, il);
+      ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, 0, q, il);
+      r.sub = sub;
       FM::run_item(P, fr, ws, dbg, f, 0, r, wave, il, wl, st);
     }
   }
@@ -74,10 +78,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   void* wl = (char*)lds + wave * M::kLds;
-  dev::level_items(FR, ws, level, [&](int f, int q) {
+  dev::level_items(FR, ws, level, M::kShares && !DBG ? P.share_groups : 0, [&](int f, int q, int sub) {
     const FrameDev& fr = FR.f[f];
     const typename M::State st = M::frame_state(ws, fr, lane);
-    const ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
+    ItemRec r = dev::find_item(P, fr, FR.n_boxes_total, ws, level, q, lane);
+    r.sub = sub;
     M::run_item(P, fr, ws, dbg, f, level, r, wave, lane, wl, st);
   });
 }

@@ -77,6 +77,8 @@ struct MatchParamsDev {
   int32_t full_census;             // whole-frame calls: 1 = census of every tile, 0 = only
                                    // of the tiles some box's search reads
   int32_t vertical;                // 1: a vertical range is searched
+  int32_t share_groups;            // launches of at most this many groups of blocks have a
+                                   // workgroup's waves share a group's vertical offsets
 };
 
 // What a path with a vertical range may ask for: nd level disparities x ndy vertical offsets
@@ -163,6 +165,7 @@ enum { GC_TIMEOUT = 0, GC_BAR0 = 8, GC_BAR1 = 16, GC_BAR2 = 24, GC_N = 32 };
 struct ItemRec {
   int32_t k;                       // box within the frame
   int32_t first;                   // the item's first group (0-based within the box)
+  int32_t sub;                     // -1, or the one group of the item that all waves take
   int32_t nblk, ngrp, off;         // the box's blocks, groups and first block number
   int32_t nbx, bw, bh, ox, oy;     // block grid
   int32_t lx0, ly0, lw, lh;        // level box
