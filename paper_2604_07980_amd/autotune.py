@@ -1,6 +1,6 @@
 """Autotuner of the matching launches: kernel variant per path shape, blocks per wave
-grid size and whether both levels share one launch, measured on the caller's own
-workload and kept in a JSON table.
+(0: by the call's size), grid size and whether both levels share one launch, measured on the
+caller's own workload and kept in a JSON table.
 
 The matching kernels come in variants (blocks or block rows per wave, candidates per
 lane) that all compute the same costs; blocks per wave and the grid size

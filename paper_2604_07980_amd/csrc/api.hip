@@ -354,7 +354,8 @@ int32_t build_params(const ocsr_ctx* ctx, const ocsr_match_params* p, int close_
 //   364 M (4 x 1200p)        49.0 / 47.6 / 50.8   730 M (8 x 1200p)      79.7 / 74.0 / 75.0
 //   933 M (4 x 1200p, 400)   83.7 / 76.6 / 74.2  1405 M (16 x 1200p)    130.5 / 121.6 / 115.9
 //  1659 M (2160p, 200)       98.2 / 91.0 / 91.6  2507 M (16 x 1200p)    205.3 / 181.1 / 174.3
-// A vertical range multiplies a group's own work: 124 M 42.5 / 55.0 / 72.1, 498 M 93.7 / 97.5 /
+// (Steps of 1 to 2% are within what one call differs by between processes, +-4%: the lines stand
+// where the larger steps begin.) A vertical range multiplies a group's own work: 124 M 42.5 / 55.0 / 72.1, 498 M 93.7 / 97.5 /
 // 109.0, 1327 M 151.1 / 138.0 / 143.3.
 void deal_items(const ocsr_ctx* ctx, const FramesDev& FR, bool fused, MatchParamsDev* d) {
   const double work = match_work(FR);

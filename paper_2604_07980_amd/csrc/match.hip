@@ -448,8 +448,9 @@ hipError_t launch_match(const MatchParamsDev& P, const FramesDev& FR, const ocsr
     // fill the close level's tail. Whole calls, one launch against two: 1080p frame 24.9 and
     // 30.6 us, 3 x 717p 23.5 and 29.0, 8 x 1200p 74.0 and 77.7, 16 x 1200p 115.9 and 118.2.
     // The kernel of both levels has more registers to spill, and past a batch of that size
-    // one launch per level is the faster: 16 x 1200p of 1088 boxes 171.9 us against 174.3;
-    // with items of one group per wave from 8 x 1200p on (79.7 against 79.8, 123.0 against 130.5)
+    // one launch per level is no slower: 16 x 1200p of 1088 boxes 171.9 us against 174.3 (within
+    // what one call differs by between processes); with items of one group per wave from
+    // 8 x 1200p on (79.7 against 79.8, 123.0 against 130.5)
     e = launch_pair(P, FR, ws, n_match_wgs, stream, timer, true) ? hipGetLastError() : hipErrorNotSupported;
     if (e != hipSuccess) return e;
   } else {

@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
 // to spill in the built code. With a vertical range, four candidates per lane would spill 50 at
 // four waves: a 1080p frame of 32 + 32 boxes over dy -3..3 takes 60 us instead of 66, a 2160p
 // one of 120 boxes 210 instead of 238. (Three, spilling 11, measure 49.5 instead of 51.3 on
-// the first but 161 instead of 158 on the second, and stay at four.)
+// the first but 161 instead of 158 on the second, and stay at four. Both with a wave walking
+// all offsets of its group.)
 template <int CPL, bool VERT = false>
 constexpr int matrix_waves() { return CPL <= (VERT ? 3 : 4) ? 4 : CPL <= 6 ? 3 : 2; }
 

@@ -149,7 +149,8 @@ struct BoxClip {
 };
 
 // Matching work is dealt in items of up to item_blocks consecutive groups of blocks of one
-// box (groups per wave x the 4 waves of a 256-thread workgroup).
+// box (groups per wave x the 4 waves of a 256-thread workgroup), or group by group where the
+// four waves share a group (share_groups).
 constexpr int kItemWaves = 4;
 constexpr int kMaxBlocksPerWave = 8;
 
@@ -225,16 +226,17 @@ hipError_t timed_launch(const LaunchTimer* timer, const char* name, void (*kerne
   return hipGetLastError();
 }
 
-// Kernel variant of one level's blocks: the register-blocked TILED kernel with `rows`
-// block rows per wave (4: blocks up to 4 x 4, 8: up to 8 x 8), `cpl` consecutive
-// candidates per lane and `passes` passes over the candidates, which covers
-// (64 / rows) * cpl * passes level candidates. Other shapes (GRID mode, wider blocks,
-// wider ranges) have no register-blocked kernel; the generic kernel takes those it covers.
+// Kernel variant of one level's blocks. rows = 1 and 2: the matrix-core matchers with four
+// blocks of up to 4 x 4 points per wave (16 cpl level candidates) and two of up to 8 x 8 (32 cpl);
+// rows = 4 and 8: the register-blocked kernel with that many block rows per wave (blocks up to
+// 4 x 4, 8 x 8), `cpl` consecutive candidates per lane and `passes` passes over them ((64 / rows)
+// cpl passes candidates); rows = 0: the generic kernel (GRID blocks, any TILED block of up to 64
+// points, up to 256 candidates).
 struct MatchVariant {
-  int tiled;           // 1: a register-blocked TILED kernel exists
+  int tiled;           // 1: a kernel covers the path
   int rows, cpl, passes;
 };
-// the default: the first built variant (in launch order) that covers the block and range
+// the default: the first built variant (in order of preference) that covers the block and range
 MatchVariant pick_variant(const PathDev& ph);
 // whether the (rows, cpl, passes) kernel is built and covers the path's blocks and range
 bool variant_valid(const PathDev& ph, int rows, int cpl, int passes);
@@ -253,7 +255,8 @@ hipError_t launch_frame_census(const MatchParamsDev& p, const FramesDev& fr,
 // Plan of every frame of a whole-frame call, with the list of the census tiles its boxes'
 // searches read (one workgroup per frame), then the census of the listed tiles by
 // persistent workgroups. Returns hipErrorNotSupported (nothing launched) when a frame has
-// more tiles than the plan step can list.
+// more tiles than the plan step can list, or the call too few for lists to pay off: below 8
+// tiles per resident workgroup slot (5 from four frames on, 3 from eight).
 hipError_t launch_plan_and_census(const MatchParamsDev& p, const FramesDev& fr,
                                   const ocsr_box* boxes, const MatchWs& ws, int sx, int sy,
                                   int sentinel, int n_cu, hipStream_t stream,
@@ -288,8 +291,9 @@ hipError_t launch_fused(const MatchParamsDev& p, const FramesDev& fr, const ocsr
 bool fused_available(const MatchParamsDev& p, const FramesDev& fr, int sx, int sy);
 
 // Dense counterpart: left-view and right-view winner-take-all over [dmin, dmax] of the
-// (2 radius + 1)^2 window sums of Hamming costs, then the left/right check. d_left and
-// d_right: int16 [H][W] scratch (d_right also an output when the caller asks for it).
+// (2 radius + 1)^2 window sums of Hamming costs, then the left/right check (launch_dense,
+// launch_dense_offsets below). disp holds the left winners until the check rewrites it; right:
+// a 32-bit word of scratch per pixel for the right ones; disp_right: null, or their int16 map.
 static_assert(sizeof(ocsr_box_point) == 64, "box point layout");
 static_assert(sizeof(ocsr_block_record) == 80, "block record layout");
 

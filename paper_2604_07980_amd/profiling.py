@@ -31,7 +31,8 @@ KERNEL_SOURCES = {
     "census": ["paper_2604_07980_amd/csrc/dev_census.hpp", "paper_2604_07980_amd/csrc/match.hip",
                "paper_2604_07980_amd/csrc/dev_match.hpp", "paper_2604_07980_amd/csrc/dev_common.hpp",
                "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
-    "match": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/dev_match.hpp",
+    "match": ["paper_2604_07980_amd/csrc/match.hip", "paper_2604_07980_amd/csrc/match_vertical.hip",
+              "paper_2604_07980_amd/csrc/dev_match.hpp",
               "paper_2604_07980_amd/csrc/dev_matrix.hpp", "paper_2604_07980_amd/csrc/dev_fp4.hpp",
               "paper_2604_07980_amd/csrc/match_kernels.hpp",
               "paper_2604_07980_amd/csrc/dev_common.hpp", "paper_2604_07980_amd/csrc/ocsr_internal.hpp"],
