@@ -99,12 +99,12 @@ __device__ __forceinline__ OccLanes box_occluders(const OccLanes& frame, const M
   return oc;
 }
 
-// Whether points (fx[q], fy) of box k lie in an occluder, all boxes of the frame scanned for those
+// Whether points (fx + q dx, fy) of box k lie in an occluder, all boxes of the frame scanned for those
 // that meet the group's rectangle [bx0, bx1] x [by0, by1] (a crowded frame's boxes have hundreds
 // of occluders, a group's rectangle few).
 template <int NM>
 __device__ __forceinline__ void scan_hidden(const MatchWs& ws, int box_off, int n, int k, int bx0, int bx1,
-                                            int by0, int by1, const int (&fx)[NM], int fy, int lane,
+                                            int by0, int by1, int fx, int dx, int fy, int lane,
                                             bool (&hidden)[NM]) {
   const BoxClip ck = ws.clip[box_off + k];
   for (int jb = 0; jb < n; jb += 256) {
@@ -123,7 +123,7 @@ __device__ __forceinline__ void scan_hidden(const MatchWs& ws, int box_off, int 
                        co[u].cy0 <= by1 && co[u].cy1 > by0;
       const uint64_t m = __ballot(occ);
 #pragma unroll
-      for (int q = 0; q < NM; ++q) hidden[q] |= in_lane_rects(m, co[u], fx[q], fy);
+      for (int q = 0; q < NM; ++q) hidden[q] |= in_lane_rects(m, co[u], fx + q * dx, fy);
     }
   }
 }
@@ -257,28 +257,25 @@ __device__ __forceinline__ void match_group(const MatchParamsDev& P, const Frame
   constexpr int NM = NB * BS * BS / 64;         // ballots: 2 (a block each) or 1 (four blocks)
   uint64_t mask[NM];
   {
-    const int bx0 = s * X0, bx1 = s * (X0 + nb * nx - 1), by0 = s * Y0, by1 = s * (Y0 + ny - 1);
     const int pi = lane & (BS - 1), pj = (lane / BS) & (BS - 1), pb = lane / (BS * BS);
-    const int fy = s * (Y0 + pj);
-    int fx[NM];
-    bool hidden[NM];
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
-      fx[q] = s * (X0 + (q + pb) * nx + pi);
-      hidden[q] = false;
-    }
-    if (oc.in_lanes) {
+    if (__builtin_expect(oc.in_lanes, 1)) {     // (the scan's code out of the way of the rest)
       const BoxClip co = oc.co;
-      const bool occ = ((oc.cand >> lane) & 1ull) && co.cx0 <= bx1 && co.cx1 > bx0 && co.cy0 <= by1 &&
-                       co.cy1 > by0;
+      const bool occ = ((oc.cand >> lane) & 1ull) && co.cx0 <= s * (X0 + nb * nx - 1) && co.cx1 > s * X0 &&
+                       co.cy0 <= s * (Y0 + ny - 1) && co.cy1 > s * Y0;
       const uint64_t m = __ballot(occ);
 #pragma unroll
-      for (int q = 0; q < NM; ++q) hidden[q] = in_lane_rects(m, co, fx[q], fy);
+      for (int q = 0; q < NM; ++q) {
+        const int b = q + pb;
+        const bool hidden = in_lane_rects(m, co, s * (X0 + b * nx + pi), s * (Y0 + pj));
+        mask[q] = __ballot(b < nb && pi < nx && pj < ny && !hidden);
+      }
     } else {
-      scan_hidden<NM>(ws, fr.box_off, fr.n_boxes, r.k, bx0, bx1, by0, by1, fx, fy, lane, hidden);
-    }
+      bool hidden[NM] = {};
+      scan_hidden<NM>(ws, fr.box_off, fr.n_boxes, r.k, s * X0, s * (X0 + nb * nx - 1), s * Y0, s * (Y0 + ny - 1),
+                      s * (X0 + pb * nx + pi), s * nx, s * (Y0 + pj), lane, hidden);
 #pragma unroll
-    for (int q = 0; q < NM; ++q) mask[q] = __ballot(q + pb < nb && pi < nx && pj < ny && !hidden[q]);
+      for (int q = 0; q < NM; ++q) mask[q] = __ballot(q + pb < nb && pi < nx && pj < ny && !hidden[q]);
+    }
   }
   auto block_mask16 = [&](int b) {              // block b's mask
     if constexpr (NB == 2) return mask[b];

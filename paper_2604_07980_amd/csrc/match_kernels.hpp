@@ -60,14 +60,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
 }
 
 // Waves per SIMD the matrix-core matchers are compiled for: their strip and accumulators grow
-// with the candidates per lane, and as many waves are taken as leave at most a dozen registers
-// to spill in the built code. With a vertical range, four candidates per lane would spill 50 at
-// four waves: a 1080p frame of 32 + 32 boxes over dy -3..3 takes 60 us instead of 66, a 2160p
-// one of 120 boxes 210 instead of 238. (Three, spilling 11, measure 49.5 instead of 51.3 on
-// the first but 161 instead of 158 on the second, and stay at four. Both with a wave walking
-// all offsets of its group.)
-template <int CPL, bool VERT = false>
-constexpr int matrix_waves() { return CPL <= (VERT ? 3 : 4) ? 4 : CPL <= 6 ? 3 : 2; }
+// with the candidates per lane, and as many waves are taken as leave few registers to spill in
+// the built code. Four candidates per lane would spill 8 at four waves: a 2160p frame of 200 boxes
+// takes 91.3 us instead of 92.8, 16 x 1200p of 40 boxes over 128 level candidates 118 instead of
+// 123 (blocks of one point, with little to spill, 443 instead of 422). With a vertical range they
+// would spill 50: a 1080p frame of 32 + 32 boxes over dy -3..3 takes 60 us instead of 66, a 2160p
+// one of 120 boxes 210 instead of 238. (Three candidates, spilling 11, measure 49.5 instead of
+// 51.3 on the first but 161 instead of 158 on the second, and stay at four waves. Both with a
+// wave walking all offsets of its group.)
+template <int CPL>
+constexpr int matrix_waves() { return CPL <= 3 ? 4 : CPL <= 6 ? 3 : 2; }
 
 // One level with any matcher. Without DBG no debug output is asked for, and its code and
 // pointers are not in the kernel.

@@ -14,7 +14,7 @@ using VQuad = dev::MatrixMatcher<4, CPL, true>;
 
 // Waves per SIMD: those of matrix_waves, but four 4 x 4 blocks per wave hold half the digits
 template <int ROWS, int CPL>
-constexpr int v_waves() { return ROWS == 2 ? matrix_waves<CPL, true>() : CPL <= 2 ? 4 : CPL <= 8 ? 3 : 2; }
+constexpr int v_waves() { return ROWS == 2 ? matrix_waves<CPL>() : CPL <= 2 ? 4 : CPL <= 8 ? 3 : 2; }
 
 hipError_t launch_level(const MatchParamsDev& P, const FramesDev& FR, const MatchWs& ws,
                         const DebugDev& dbg, int level, int grid, hipStream_t stream,
